@@ -23,21 +23,25 @@ struct ScoreArgs {
   const void* k;          // [B][Hkv][Lmax][d]
   float* scores;          // [B][Hkv][Lmax]
   float* raw_scores;      // nullable, same layout
-  float* e;               // ws: [B][Hkv][n_tiles][R][64] exp(s - tile max), fp32
-  double* tile_m;         // ws: [B][Hkv][R][n_tiles]
-  double* tile_z;         // ws: [B][Hkv][R][n_tiles]
+  float* e;               // ws: [B][Hkv][n_tiles][4][R][16] exp(s - tile reference), fp32
+                          //     (key 16 k + j of a tile at [k][row][j])
+  double* tile_m;         // ws: [B][Hkv][n_tiles][R] tile reference (logit units)
+  double* tile_z;         // ws: [B][Hkv][n_tiles][R] sum of the row's e
   double* row_M;          // ws: [B][Hkv][R]
   double* row_Z;          // ws: [B][Hkv][R]
   float* raw;             // raw scores: raw_scores if given, else ws [B][Hkv][Lmax]
   int32_t B, Lmax, Hq, Hkv, w, pool, R, n_tiles, row_chunks;
   int32_t pool_avg;       // 0: max-pool, 1: mean over the window (zeros outside the prefix)
   int32_t stream_e;       // set by launch_score: e written with streaming stores
-  int32_t pack_pairs;     // set by launch_score: row pairs P of packed K1 blocks, 0 if unpacked
+  int32_t pack_pairs;     // set by launch_score: row pairs P of packed fp32 K1 blocks, 0 if unpacked
+  int32_t run;            // set by launch_score_tiles_bf16: tiles per block,
+  int32_t blk_off[kMaxB]; //   first block of each sequence
   double scale;           // 1/sqrt(d)
   int32_t L[kMaxB];
 };
 size_t score_ws_bytes(int B, int Lmax, int Hkv, int R);
 hipError_t launch_score(const ScoreArgs& a, int d, bool bf16, hipStream_t st);
+hipError_t launch_score_tiles_bf16(const ScoreArgs& a, int d, hipStream_t st);  // K1, bf16
 
 // ---------------------------------------------------------------- KNorm
 struct KnormArgs {

@@ -1,0 +1,283 @@
+// K1 of the observation-window scoring for bf16 inputs: the softmax numerators
+// of every (window row, key) pair, on the int8 matrix cores (exact_dot.h).
+//
+// Block = 1, 2, 4 or 8 waves of 32 window rows of one KV head (chunks of 256
+// rows past that) over a run of consecutive 64-key tiles.  A wave converts its
+// rows to digit planes once and keeps them in registers; each tile's keys are
+// read from HBM once per block (one tile ahead, into registers), converted by
+// all waves, those without rows included, and shared through LDS.
+// Per 16-key step a wave computes 13 digit products for each of its two 16-row
+// column tiles, recombines them to the logit (base-2 units) in float64, splits
+// it as t = n + f and takes 2^f in fp32.  Keys are the MFMA rows, so a lane
+// holds 16 keys of one window row.  e is 2^(t - ref) with an integer reference
+// (only the exponent shifts), taken from the tile before, so e is stored step
+// by step and no logit waits in registers for the tile's maximum; a tile that
+// the reference does not fit is redone.  Stores e (fp32, float4 of 4
+// consecutive keys, laid out [tile][16-key step][row][16]) and per (tile, row)
+// the reference in logit units and the sum.
+
+#include <type_traits>
+
+#include "exact_dot.h"
+#include "kernels.h"
+
+namespace tb {
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4n;
+constexpr int kT = kScoreTile;
+constexpr int kNone = -(1 << 29);            // n of a masked logit
+// A tile's reference is the row's largest n of the tile before; it stands
+// while the tile's own largest n lies kRefLow .. kRefLow + kRefSpan above it
+// (e between 2^-102 of the largest and 2^60 keeps its fp32 precision).
+constexpr int kRefLow = -24, kRefSpan = 84;
+
+template <int D, int WAVES, bool STREAM>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
+void score_tiles_i8_kernel(ScoreArgs a) {
+  using Tile = StreamTile<D>;
+  constexpr int MP = Tile::NG > WAVES ? Tile::NG / WAVES : 1;   // staging groups per wave
+  constexpr bool kTwo = WAVES >= 4;          // two LDS buffers and keys fetched a tile ahead
+  constexpr int kWin = MP < 4 ? MP : 4;      // groups held in registers
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q4 = lane >> 4, r16 = lane & 15;
+  // block -> (sequence, KV head, row chunk, run of tiles)
+  int b = 0;
+  while (b + 1 < a.B && static_cast<int>(blockIdx.x) >= a.blk_off[b + 1]) ++b;
+  const int L = a.L[b], nt = (L + kT - 1) / kT;
+  const int runs = (nt + a.run - 1) / a.run;
+  const int idx = static_cast<int>(blockIdx.x) - a.blk_off[b];
+  const int unit = idx / runs;
+  const int t_lo = (idx % runs) * a.run, t_hi = min(t_lo + a.run, nt);
+  const int g = unit / a.row_chunks, row0 = (unit % a.row_chunks) * kScoreRows + 32 * wave;
+  const int G = a.Hq / a.Hkv, R = a.R, w = a.w;
+  const size_t bg = static_cast<size_t>(b) * a.Hkv + g;
+  const uint16_t* kg = static_cast<const uint16_t*>(a.k) + bg * a.Lmax * D;
+  const bool active = row0 < R;              // wave-uniform
+
+  __shared__ Tile s_tile[kTwo ? 2 : 1];
+
+  // this wave's staging groups are wave * MP + u; rows past the prompt: any
+  // valid row (masked)
+  const bool stager = wave * MP < Tile::NG;  // wave-uniform
+  uint4 raw[kWin];
+  // (addresses: a wave-uniform base and a 32-bit lane offset, here and below)
+  auto fetch = [&](int tile, int u) {
+    const int k0 = min(tile, nt - 1) * kT;
+    const int key = min((wave * MP + u) * Tile::RPG + lane / Tile::LPR, L - 1 - k0);
+    uint32_t off = (key * D + 8 * (lane % Tile::LPR)) * 2;
+    return ldg16(reinterpret_cast<const char*>(kg + static_cast<size_t>(k0) * D) + off);
+  };
+  if (kTwo && stager) {
+#pragma unroll
+    for (int u = 0; u < kWin; ++u) raw[u] = fetch(t_lo, u);
+  }
+
+  Stationary<D> sx;
+  int row[2];                                // padding rows repeat row R - 1
+  const uint16_t* col[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    row[c] = min(row0 + 16 * c + r16, R - 1);
+    col[c] = static_cast<const uint16_t*>(a.q_win) +
+             ((static_cast<size_t>(b) * a.Hq + g * G + row[c] / w) * w + row[c] % w) * D;
+  }
+  sx.load(col, q4);
+  const double cd = a.scale * 1.4426950408889634;           // exp(x) = 2^(x log2 e)
+  const float cf = static_cast<float>(cd);
+  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p24),
+                        static_cast<double>(sx.unit[1]) * (cd * 0x1p24)};
+  // wave-uniform: scalar registers
+  const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
+  const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
+
+  // stage a tile and wait for it; the waves of a block call this for the same
+  // tiles, so they meet the same barriers
+  auto stage = [&](int tile) -> Tile& {
+    Tile& st = s_tile[kTwo ? (tile - t_lo) & 1 : 0];
+    if (!kTwo && tile > t_lo) __syncthreads();              // the previous tile has been read
+    if (stager) {
+      uint32_t flags = 0u;
+#pragma unroll
+      for (int u0 = 0; u0 < MP; u0 += kWin) {
+        if (!kTwo) {
+#pragma unroll
+          for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile, u0 + u);
+        }
+#pragma unroll
+        for (int u = 0; u < kWin; ++u) flags |= st.put(wave * MP + u0 + u, lane, raw[u]);
+      }
+      if (__builtin_amdgcn_ballot_w64(flags != 0u))         // rare: the groups get their bounds
+        for (int u = 0; u < MP; ++u) st.put_bound(wave * MP + u, lane, fetch(tile, u));
+      if (kTwo) {
+#pragma unroll
+        for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile + 1, u);
+      }
+    }
+    __syncthreads();
+    return st;
+  };
+  if (!active) {
+    for (int tile = t_lo; tile < t_hi; ++tile) stage(tile);
+    return;
+  }
+
+  int ref[2] = {0, 0};                       // of this lane's rows, base-2 units
+  for (int tile = t_lo; tile < t_hi; ++tile) {
+    Tile& st = stage(tile);
+    const int kbase = tile * kT;
+    const bool edge = kbase + kT > L - w;                   // some rows do not see all 64 keys
+    int lim[2] = {63, 63};                                  // last key the rows see
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (edge) lim[c] = min(L - 1, L - w + row[c] % w) - kbase - 4 * q4;
+    // Every lane stores, the same count on every path: the four lane groups
+    // hold the same sum, and padding rows are copies of row R - 1.  So a wait
+    // for the keys fetched before the stores need not wait for the stores.
+    const size_t te = (bg * a.n_tiles + tile) * R;
+    auto store_e = [&](int c, int kt, const float (&e)[4]) {
+      const f32x4n x = {e[0], e[1], e[2], e[3]};
+      uint32_t off = (row[c] * 16 + 4 * q4) * 4;
+      asm volatile("" : "+v"(off));          // added here, not once per step ahead of the loop
+      f32x4n* p = reinterpret_cast<f32x4n*>(
+          reinterpret_cast<char*>(a.e + (te * 4 + static_cast<size_t>(kt) * R) * 16) + off);
+      if constexpr (STREAM) __builtin_nontemporal_store(x, p);
+      else                  *p = x;
+      return static_cast<double>((e[0] + e[1]) + (e[2] + e[3]));
+    };
+    double m[2], z[2] = {0.0, 0.0};
+    if (st.exact_enough(U, V, cf, lane)) {
+      // false: a reference did not fit, and has been set
+      auto pass = [&](auto masked) -> bool {
+        asm volatile("" ::: "memory");       // no operand is read ahead of the pass
+        int top[2] = {kNone, kNone};
+        z[0] = z[1] = 0.0;
+        pipelined_products<D>(st, sx, q4, r16, [&](int kt, int c, const i32x4 (&S)[kSums]) {
+          const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
+          float e[4];
+          int n[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const double v = digit_value(S, i);
+            // the sum with 1.5 2^52 holds round(t), t = v f, in its low word
+            // (|t| < 2^18 here)
+            const double y = fma(v, f, 0x1.8p52);
+            n[i] = static_cast<int>(static_cast<uint32_t>(__double_as_longlong(y)));
+            e[i] = ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(fma(v, f, 0x1.8p52 - y))), n[i] - ref[c]);
+          }
+          if constexpr (decltype(masked)::value) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const bool ok = 16 * kt + i <= lim[c];
+              n[i] = ok ? n[i] : kNone;
+              e[i] = ok ? e[i] : 0.f;
+            }
+          }
+          top[c] = max(max(top[c], max(n[0], n[1])), max(n[2], n[3]));
+          z[c] += store_e(c, kt, e);
+        });
+        bool bad = false;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int t = static_cast<int>(group_all(static_cast<uint32_t>(top[c]), IMax()));
+          const int over = t == kNone ? 0 : t - ref[c];
+          m[c] = static_cast<double>(ref[c]) * 0.69314718055994530942;
+          ref[c] += over;                    // the next tile's reference
+          bad = bad || over > kRefLow + kRefSpan || over < kRefLow;
+        }
+        return __builtin_amdgcn_ballot_w64(bad) == 0;
+      };
+      // the masked pass serves the last tiles and (twice at most) a reference
+      // that does not fit
+      bool done = !edge && pass(std::false_type());
+      while (!done) done = pass(std::true_type());
+    } else {
+      // the same with float64 products; only the reference may be any float64
+      double rd[2] = {static_cast<double>(ref[0]), static_cast<double>(ref[1])};
+      for (int round = 0;; ++round) {
+        float mx[2] = {-INFINITY, -INFINITY};
+        z[0] = z[1] = 0.0;
+#pragma unroll 1
+        for (int kt = 0; kt < 4; ++kt) {
+          f64x4 acc[2];
+          const int key = min(kbase + 16 * kt + 4 * (r16 & 3) + (r16 >> 2), L - 1);
+          f64_products<D>(kg + static_cast<size_t>(key) * D, col, q4, acc);
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            float e[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double t = fma(acc[c][i], cd, -rd[c]);
+              const bool ok = 16 * kt + i <= lim[c];
+              mx[c] = ok ? fmaxf(mx[c], static_cast<float>(t)) : mx[c];
+              e[i] = ok ? exp2_split(t) : 0.f;
+            }
+            z[c] += store_e(c, kt, e);
+          }
+        }
+        bool redo = false;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          mx[c] = fmaxf(mx[c], __shfl_xor(mx[c], 16));
+          mx[c] = fmaxf(mx[c], __shfl_xor(mx[c], 32));
+          m[c] = rd[c] * 0.69314718055994530942;
+          const bool off = round == 0 && fabsf(mx[c]) < INFINITY && !(mx[c] <= kRefLow + kRefSpan && mx[c] >= kRefLow);
+          if (off) rd[c] += rint(static_cast<double>(mx[c]));
+          redo = redo || off;
+        }
+        if (__builtin_amdgcn_ballot_w64(redo) == 0) break;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      uint32_t mo = row[c] * 8;
+      asm volatile("" : "+v"(mo));
+      *reinterpret_cast<double*>(reinterpret_cast<char*>(a.tile_m + te) + mo) = m[c];
+      *reinterpret_cast<double*>(reinterpret_cast<char*>(a.tile_z + te) + mo) = group_sum_f64(z[c]);
+    }
+  }
+}
+
+template <int D, int WAVES>
+void launch_w(const ScoreArgs& a, int blocks, hipStream_t st) {
+  if (a.stream_e) score_tiles_i8_kernel<D, WAVES, true><<<blocks, 64 * WAVES, 0, st>>>(a);
+  else            score_tiles_i8_kernel<D, WAVES, false><<<blocks, 64 * WAVES, 0, st>>>(a);
+}
+
+template <int D>
+hipError_t launch_d(const ScoreArgs& a, int blocks, int waves, hipStream_t st) {
+  switch (waves) {
+    case 8:  launch_w<D, 8>(a, blocks, st); break;
+    case 4:  launch_w<D, 4>(a, blocks, st); break;
+    case 2:  launch_w<D, 2>(a, blocks, st); break;
+    default: launch_w<D, 1>(a, blocks, st); break;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_score_tiles_bf16(const ScoreArgs& args, int d, hipStream_t st) {
+  ScoreArgs a = args;
+  int waves = 1;
+  while (waves < 8 && 32 * waves < a.R) waves *= 2;
+  // Two waves per SIMD fit a CU (registers), so 8 / waves blocks, up to 4
+  // (LDS: 64 KB for 4 or 8 waves, 32 KB below).  One round of blocks over the
+  // chip, each taking a run of tiles as long as that needs, since a block
+  // first converts its rows.
+  const int per_cu = waves >= 2 ? 8 / waves : 4;
+  long long total = 0;
+  for (int b = 0; b < a.B; ++b) total += (a.L[b] + kT - 1) / kT;
+  total *= static_cast<long long>(a.Hkv) * a.row_chunks;
+  a.run = static_cast<int32_t>((total + 256 * per_cu - 1) / (256 * per_cu));
+  int blocks = 0;
+  for (int b = 0; b < a.B; ++b) {
+    a.blk_off[b] = blocks;
+    const int nt = (a.L[b] + kT - 1) / kT;
+    blocks += (nt + a.run - 1) / a.run * a.Hkv * a.row_chunks;
+  }
+  return d == 128 ? launch_d<128>(a, blocks, waves, st) : launch_d<64>(a, blocks, waves, st);
+}
+
+}  // namespace tb

@@ -9,22 +9,25 @@
 // single-precision values; pooling is a max, so it is exact.
 //
 // Four kernels, all with fixed-order reductions (no atomics):
-//   K1 score_tiles: block = (64-key tile, <=256 window rows) of one KV head,
-//      512 threads; wave w owns 32 rows x the 64 keys (waves whose rows are all
-//      padding skip the products).  With 4, 6 or 7 row pairs and enough
-//      blocks, a block instead takes 8 consecutive units (32 rows x one tile,
-//      numbered tile-major) over at most two tiles, so no wave idles.
-//      Window queries (as fp32) and keys (as
-//      float64, converted once since every wave reads them) are staged in LDS
-//      in 32-wide d chunks, the next chunk's global loads in flight while the
-//      current one is multiplied; the float64 dot products run on the matrix
-//      cores (v_mfma_f64_16x16x4_f64, 2 x 4 tiles of 16 x 16 per wave).  Each
-//      row's 64 logits sit in one 16-lane DPP row, so the causal mask, a tile
-//      reference m (the row's largest dot product rounded to fp32) and
-//      z = sum exp(s - m) need no LDS.  Stores e = exp(s - m) (fp32, one float4
-//      per lane and row: keys r, r+16, r+32, r+48) and (m, z) per (row, tile).
-//   K2 row_stats: one wave per window row merges its tiles' (m, z) into the
-//      row's global max M and normaliser Z.
+//   K1 score_tiles: the softmax numerators e = exp(s - m) (fp32) of every
+//      (window row, key) with a reference m per (row, 64-key tile), and
+//      z = sum e.  bf16: exact digit products on the int8 matrix cores
+//      (score_tiles_bf16.hip; L = 131072, 8 KV heads, 256 rows: 417 us against
+//      1241 with the float64 products, L = 8192, 4 KV heads, 224 rows: 25
+//      against 46).  fp32 (below): block = (64-key tile, <= 256 window rows) of
+//      one KV head, 512 threads; wave w owns 32 rows x the 64 keys (waves
+//      whose rows are all padding skip the products).  With 4, 6 or 7 row
+//      pairs and enough blocks, a block instead takes 8 consecutive units (32
+//      rows x one tile, numbered tile-major) over at most two tiles, so no
+//      wave idles.  Window queries (as fp32) and keys (as float64, converted
+//      once since every wave reads them) are staged in LDS in 32-wide d
+//      chunks, the next chunk's global loads in flight while the current one
+//      is multiplied; the products run on the float64 matrix cores
+//      (v_mfma_f64_16x16x4_f64, 2 x 4 tiles of 16 x 16 per wave).  Each row's
+//      64 logits sit in one 16-lane DPP row, so the causal mask, m (the row's
+//      largest dot product rounded to fp32) and z need no LDS.
+//   K2 row_stats: each window row's global max M and normaliser Z from its
+//      tiles' (m, z).
 //   K3 score_accum: block = 64 prefix columns; A[j] = sum_r e[r][j] *
 //      exp(m[r][tile] - M[r]) / Z[r] in float64 (four row groups, four
 //      independent accumulators each, combined in a fixed order); raw A as fp32.
@@ -32,18 +35,16 @@
 //      (or their mean with zeros outside the prefix and divisor pool, summed in
 //      float64, for the average-pool variant).
 //
-// The per-logit exponential is the one place fp64 arithmetic is avoided: on
-// this part the fp64 vector instructions compete with the fp64 matrix
-// instructions for the same throughput, so K1's epilogue reduces the argument
-// in fp64 (exactly) and evaluates 2^f for |f| <= 1/2 in fp32.
+// The per-logit exponential is the one place fp64 arithmetic is avoided: K1's
+// epilogue reduces the argument in fp64 (exactly) and evaluates 2^f for
+// |f| <= 1/2 in fp32.
 
-#include "common.h"
+#include "exact_dot.h"
 #include "kernels.h"
 
 namespace tb {
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) double f64x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4n;
 
 constexpr int kThreads = 256;
@@ -51,25 +52,9 @@ constexpr int kT = kScoreTile;     // keys per tile (64)
 constexpr int kRows = kScoreRows;  // rows per block (256)
 constexpr int kDC = 32;            // d chunk staged in LDS
 
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float* out);
-template <>
-__device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float* out) {
-  Elem<bf16_t>::widen(ldg16(p), out);
-}
-template <>
-__device__ __forceinline__ void load8<float>(const float* p, float* out) {
+__device__ __forceinline__ void load8(const float* p, float* out) {
   Elem<float>::widen(ldg16(p), out);
   Elem<float>::widen(ldg16(p + 4), out + 4);
-}
-
-// 2^t as fp32 for a float64 t >= -300: t = n + f with n = round(t) exact and
-// |f| <= 1/2, so only f is rounded to fp32 (relative effect on 2^f below
-// 3e-8); 2^f comes from the hardware base-2 exponential (about 1 ulp) and the
-// scaling by 2^n is exact (results under the smallest fp32 subnormal are 0).
-__device__ __forceinline__ float exp2_split(double t) {
-  const double n = rint(t);
-  return ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - n)), static_cast<int>(n));
 }
 
 template <int CTRL>
@@ -112,7 +97,7 @@ constexpr int kWaveRows = 32;      // window rows per wave in score_tiles
 // tiles, whose keys it stages together.  With one idle wave per block (R =
 // 224) the busiest SIMD of a CU carries as many waves as at R = 256 and the
 // block barriers pace every block by it; packing gives each block 8 busy waves.
-template <typename T, int D, int NS>
+template <int D, int NS>
 __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs a) {
   const int g = blockIdx.y, b = blockIdx.z;
   const int L = a.L[b];
@@ -150,26 +135,29 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
   // per key (8 elements each; the first 256 threads when NS = 1).
   const int qrow = tid >> 1, qoff = (tid & 1) * 16;
   const bool qvalid = row0 + qrow < R;
-  const T* qsrc = nullptr;
+  const float* qsrc = nullptr;
   if (qvalid) {
     const int r = row0 + qrow, h = g * G + r / w, i = r % w;
-    qsrc = static_cast<const T*>(a.q_win) + ((static_cast<size_t>(b) * a.Hq + h) * w + i) * D + qoff;
+    qsrc = static_cast<const float*>(a.q_win) + ((static_cast<size_t>(b) * a.Hq + h) * w + i) * D + qoff;
   }
   const int kk = (tid & (NS * 256 - 1)) >> 2, kdp = (tid & 3) * 8;
+  // key kk of a tile sits in LDS row 16 (kk % 4) + kk / 4, so the product's
+  // column r16 of step kt is key 4 r16 + kt: a lane's 4 keys are consecutive
+  const int krow = (kk & ~63) | ((kk & 3) << 4) | ((kk & 63) >> 2);
   const bool kvalid = tid < NS * 256 && t0 * kT + kk < L;
-  const T* ksrc = static_cast<const T*>(a.k) +
+  const float* ksrc = static_cast<const float*>(a.k) +
                   ((static_cast<size_t>(b) * a.Hkv + g) * a.Lmax + t0 * kT + kk) * D + kdp;
   float qv[16], kv[8];
   auto fetch = [&](int dc) {
     if (qvalid) {
-      load8<T>(qsrc + dc, qv);
-      load8<T>(qsrc + dc + 8, qv + 8);
+      load8(qsrc + dc, qv);
+      load8(qsrc + dc + 8, qv + 8);
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) qv[e] = 0.f;
     }
     if (kvalid) {
-      load8<T>(ksrc + dc, kv);
+      load8(ksrc + dc, kv);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) kv[e] = 0.f;
@@ -180,7 +168,7 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
     for (int e = 0; e < 16; ++e) qs[qrow][qoff + e] = qv[e];
     if (tid < NS * 256) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ks[kk][kdp + e] = static_cast<double>(kv[e]);
+      for (int e = 0; e < 8; ++e) ks[krow][kdp + e] = static_cast<double>(kv[e]);
     }
   };
 
@@ -222,7 +210,7 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
   }
   if (!active) return;
 
-  // acc[rt][kt][v] = q(row 16 rt + q4 + 4 v) . k(key 16 kt + r16) of this wave
+  // acc[rt][kt][v] = q(row 16 rt + q4 + 4 v) . k(key 4 r16 + kt) of this wave
   // (the float64 16x16x4 product returns rows interleaved: item v of lane l is
   // row l/16 + 4v, column l%16).
   const size_t bg = static_cast<size_t>(b) * a.Hkv + g;
@@ -238,7 +226,7 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
       float mx = -INFINITY;
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt) {
-        ok[kt] = kbase + 16 * kt + r16 <= lim;
+        ok[kt] = kbase + 4 * r16 + kt <= lim;
         mx = fmaxf(mx, ok[kt] ? static_cast<float>(acc[rt][kt][v]) : -INFINITY);
       }
       // reference: the row's largest dot product rounded to fp32 (exact as a
@@ -254,12 +242,12 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
       const double z = row16_sum_f64(static_cast<double>(zs));
       const int rg = row0 + rl;
       if (rg < R) {
-        float* dst = ebase + static_cast<size_t>(rg) * kT + 4 * r16;
+        float* dst = ebase + (static_cast<size_t>(r16 >> 2) * R + rg) * 16 + 4 * (r16 & 3);
         if (a.stream_e) __builtin_nontemporal_store(f32x4n{ev[0], ev[1], ev[2], ev[3]},
                                                     reinterpret_cast<f32x4n*>(dst));
         else            *reinterpret_cast<float4*>(dst) = make_float4(ev[0], ev[1], ev[2], ev[3]);
         if (r16 == 0) {
-          const size_t o = (bg * R + rg) * a.n_tiles + tile;
+          const size_t o = (bg * a.n_tiles + tile) * R + rg;
           a.tile_m[o] = md * a.scale;       // -inf when the whole row-tile is masked
           a.tile_z[o] = z;
         }
@@ -268,52 +256,59 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
   }
 }
 
-// One wave per (b, g, row): global max and normaliser over the row's tiles.
-__global__ __launch_bounds__(kThreads) void row_stats_kernel(ScoreArgs a) {
-  const int wid = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int total = a.B * a.Hkv * a.R;
-  if (wid >= total) return;
-  const int r = wid % a.R;
-  const int bg = wid / a.R;
-  const int b = bg / a.Hkv;
+// Global max and normaliser of 16 rows per block over their tiles: thread
+// (phase, row) merges the row's tiles phase, phase + 64, ..., eight at a time
+// (16 rows' values are one 128-byte line), then the phases are merged.
+constexpr int kStatRows = 16, kStatPhases = 64, kStatThreads = kStatRows * kStatPhases;
+__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(ScoreArgs a) {
+  const int g = blockIdx.y, b = blockIdx.z;
+  const int rr = threadIdx.x % kStatRows, ph = threadIdx.x / kStatRows;
+  const int r = blockIdx.x * kStatRows + rr;
   const int nt = (a.L[b] + kT - 1) / kT;
-  const size_t rowo = (static_cast<size_t>(bg) * a.R + r) * a.n_tiles;
-  double M = -INFINITY, Z = 0.0;
-  // the lane's tiles t = lane, lane + 64, ... in that order, their loads
-  // issued 8 at a time ahead of the merge (one memory round trip per 8)
+  const size_t bg = static_cast<size_t>(b) * a.Hkv + g;
+  const size_t o = bg * a.n_tiles * a.R + min(r, a.R - 1);
+  constexpr int kWaves = kStatThreads / 64;
+  __shared__ double s_m[kWaves][kStatRows], s_z[kWaves][kStatRows];
   constexpr int kAhead = 8;
-  for (int t0 = lane; t0 < nt; t0 += 64 * kAhead) {
-    double mv[kAhead], zv[kAhead];
+  double M = -INFINITY, Z = 0.0;
+  for (int t0 = ph; t0 < nt; t0 += kStatPhases * kAhead) {
+    double mv[kAhead], zv[kAhead], top = M;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
-      const int t = min(t0 + 64 * k, nt - 1);
-      mv[k] = a.tile_m[rowo + t];
-      zv[k] = a.tile_z[rowo + t];
+      const int t = t0 + kStatPhases * k;
+      const size_t p = o + static_cast<size_t>(min(t, nt - 1)) * a.R;
+      mv[k] = a.tile_m[p];
+      zv[k] = a.tile_z[p];
     }
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
-      const double m = mv[k], z = zv[k];
-      if (t0 + 64 * k >= nt || m == -INFINITY) continue;
-      if (m > M) { Z = Z * exp(M - m) + z; M = m; }
-      else       { Z += z * exp(m - M); }
+      if (t0 + kStatPhases * k >= nt) mv[k] = -INFINITY;
+      top = fmax(top, mv[k]);
     }
-  }
+    if (M != -INFINITY) Z *= exp(M - top);
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    // Both partners evaluate the same expression with the same operand order
-    // (lower lane first), so every lane ends with bit-identical (M, Z).
-    const double Mo = __shfl_xor(M, off), Zo = __shfl_xor(Z, off);
-    const bool upper = (lane & off) != 0;
-    const double Ma = upper ? Mo : M, Za = upper ? Zo : Z;
-    const double Mb = upper ? M : Mo, Zb = upper ? Z : Zo;
-    const double Mn = fmax(Ma, Mb);
-    Z = (Mn == -INFINITY) ? 0.0 : Za * exp(Ma - Mn) + Zb * exp(Mb - Mn);
-    M = Mn;
+    for (int k = 0; k < kAhead; ++k)
+      if (mv[k] != -INFINITY) Z += zv[k] * exp(mv[k] - top);
+    M = top;
   }
-  if (lane == 0) {
-    a.row_M[static_cast<size_t>(bg) * a.R + r] = M;
-    a.row_Z[static_cast<size_t>(bg) * a.R + r] = Z;
+  const double own = M;
+  M = fmax(M, __shfl_xor(M, 16));
+  M = fmax(M, __shfl_xor(M, 32));
+  if ((threadIdx.x & 63) < kStatRows) s_m[threadIdx.x >> 6][rr] = M;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) M = fmax(M, s_m[k][rr]);
+  Z = own == -INFINITY ? 0.0 : Z * exp(own - M);
+  Z += __shfl_xor(Z, 16);
+  Z += __shfl_xor(Z, 32);
+  if ((threadIdx.x & 63) < kStatRows) s_z[threadIdx.x >> 6][rr] = Z;
+  __syncthreads();
+  if (ph == 0 && r < a.R) {
+    Z = s_z[0][rr];
+#pragma unroll
+    for (int k = 1; k < kWaves; ++k) Z += s_z[k][rr];
+    a.row_M[bg * a.R + r] = M;
+    a.row_Z[bg * a.R + r] = Z;
   }
 }
 
@@ -331,18 +326,18 @@ __global__ __launch_bounds__(kThreads) void score_accum_kernel(ScoreArgs a) {
   __shared__ double part[16][kT];
 
   for (int r = tid; r < R; r += kThreads) {
-    const double m = a.tile_m[(bg * R + r) * a.n_tiles + ct];
+    const double m = a.tile_m[(bg * a.n_tiles + ct) * R + r];
     const double M = a.row_M[bg * R + r], Z = a.row_Z[bg * R + r];
     coef[r] = (m != -INFINITY && Z > 0.0) ? exp(m - M) / Z : 0.0;
   }
   __syncthreads();
-  // Key col of a tile row is stored at 4 (col % 16) + col / 16, so the 16-byte
-  // vector at 4 q holds cols q, q + 16, q + 32, q + 48.  Thread (q, rs) reads
-  // those vectors from rows rs, rs + 16, ..., eight loads in flight, and keeps
-  // four float64 column sums; the 16 row phases are then added in order.
+  // Thread (q, rs) reads the float4 of columns 4 q .. 4 q + 3 from rows rs,
+  // rs + 16, ..., eight loads in flight, and keeps four float64 column sums;
+  // the 16 row phases are then added in order.
   // (Sixteen loads in flight, issued before the coefficients, measured slower.)
   const int q = tid & 15, rs = tid >> 4;
-  const float* et = a.e + (bg * a.n_tiles + ct) * static_cast<size_t>(R) * kT + 4 * q;
+  const float* et = a.e + (bg * a.n_tiles + ct) * static_cast<size_t>(R) * kT +
+                    static_cast<size_t>(q >> 2) * R * 16 + 4 * (q & 3);
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
   constexpr int kBatch = 8;
   for (int rb = rs; rb < R; rb += 16 * kBatch) {
@@ -350,7 +345,7 @@ __global__ __launch_bounds__(kThreads) void score_accum_kernel(ScoreArgs a) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int r = rb + 16 * u;
-      v[u] = r < R ? *reinterpret_cast<const float4*>(et + static_cast<size_t>(r) * kT)
+      v[u] = r < R ? *reinterpret_cast<const float4*>(et + static_cast<size_t>(r) * 16)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
@@ -363,10 +358,10 @@ __global__ __launch_bounds__(kThreads) void score_accum_kernel(ScoreArgs a) {
       s3 = fma(static_cast<double>(v[u].w), c, s3);
     }
   }
-  part[rs][q] = s0;
-  part[rs][q + 16] = s1;
-  part[rs][q + 32] = s2;
-  part[rs][q + 48] = s3;
+  part[rs][4 * q] = s0;
+  part[rs][4 * q + 1] = s1;
+  part[rs][4 * q + 2] = s2;
+  part[rs][4 * q + 3] = s3;
   __syncthreads();
   if (tid < kT) {
     const int j = j0 + tid;
@@ -400,6 +395,37 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(ScoreArgs a) {
   }
 }
 
+hipError_t launch_tiles_f32(const ScoreArgs& args, int d, hipStream_t st) {
+  ScoreArgs a = args;
+  // Packed blocks (P = 4, 6 or 7 row pairs: waves would idle, and every run of
+  // 8 units spans at most two tiles) when packing lowers the blocks per CU and
+  // still leaves two per CU (two resident blocks overlap each other's barriers
+  // and staging).  Measured, d = 128, one scoring call, packed against not
+  // (us): P = 7, 4 KV heads: L = 32768 174 / 187 (8 -> 7 blocks per CU),
+  // 36864 198 / 210, 65536 352 / 369, but 8192 64.0 / 62.5, 16384 107 / 105,
+  // 24576 157 / 153, 28672 175 / 169 (blocks per CU unchanged); P = 6:
+  // 16384 85.0 / 99.7, 32768 152 / 184, 8192 60.1 / 59.2 (2 -> 2); P = 4:
+  // 16384 60.9 / 66.6, 32768 107 / 117, 8192 43.9 / 40.8 (one block per CU).
+  constexpr long long kCUs = 256;
+  const int P = (a.R + kWaveRows - 1) / kWaveRows;
+  const long long units = static_cast<long long>(a.Hkv) * a.B;
+  const long long plain = static_cast<long long>(a.n_tiles) * units;
+  const long long packed = (static_cast<long long>(P) * a.n_tiles + 7) / 8 * units;
+  const bool pack = a.row_chunks == 1 && (P == 4 || P == 6 || P == 7) && packed >= 2 * kCUs &&
+                    (packed + kCUs - 1) / kCUs < (plain + kCUs - 1) / kCUs;
+  a.pack_pairs = pack ? P : 0;
+  if (pack) {
+    const dim3 g1((P * a.n_tiles + 7) / 8, a.Hkv, a.B);
+    if (d == 128) score_tiles_kernel<128, 2><<<g1, kTilesThreads, 0, st>>>(a);
+    else          score_tiles_kernel<64, 2><<<g1, kTilesThreads, 0, st>>>(a);
+  } else {
+    const dim3 g1(a.n_tiles * a.row_chunks, a.Hkv, a.B);
+    if (d == 128) score_tiles_kernel<128, 1><<<g1, kTilesThreads, 0, st>>>(a);
+    else          score_tiles_kernel<64, 1><<<g1, kTilesThreads, 0, st>>>(a);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 size_t score_ws_bytes(int B, int Lmax, int Hkv, int R) {
@@ -422,46 +448,9 @@ hipError_t launch_score(const ScoreArgs& args, int d, bool bf16, hipStream_t st)
   ScoreArgs a = args;
   const double e_bytes = 4.0 * kT * a.R * a.n_tiles * a.Hkv * a.B;
   a.stream_e = e_bytes > 256.0 * (1 << 20);
-  // Packed blocks (P = 4, 6 or 7 row pairs: waves would idle, and every run of
-  // 8 units spans at most two tiles) when packing lowers the blocks per CU and
-  // still leaves two per CU (two resident blocks overlap each other's barriers
-  // and staging).  Measured, d = 128, one scoring call, packed against not
-  // (us): P = 7, 4 KV heads: L = 32768 174 / 187 (8 -> 7 blocks per CU),
-  // 36864 198 / 210, 65536 352 / 369, but 8192 64.0 / 62.5, 16384 107 / 105,
-  // 24576 157 / 153, 28672 175 / 169 (blocks per CU unchanged); P = 6:
-  // 16384 85.0 / 99.7, 32768 152 / 184, 8192 60.1 / 59.2 (2 -> 2); P = 4:
-  // 16384 60.9 / 66.6, 32768 107 / 117, 8192 43.9 / 40.8 (one block per CU).
-  constexpr long long kCUs = 256;
-  const int P = (a.R + kWaveRows - 1) / kWaveRows;
-  const long long units = static_cast<long long>(a.Hkv) * a.B;
-  const long long plain = static_cast<long long>(a.n_tiles) * units;
-  const long long packed = (static_cast<long long>(P) * a.n_tiles + 7) / 8 * units;
-  const bool pack = a.row_chunks == 1 && (P == 4 || P == 6 || P == 7) && packed >= 2 * kCUs &&
-                    (packed + kCUs - 1) / kCUs < (plain + kCUs - 1) / kCUs;
-  a.pack_pairs = pack ? P : 0;
-  if (pack) {
-    const dim3 g1((P * a.n_tiles + 7) / 8, a.Hkv, a.B);
-    if (bf16) {
-      if (d == 128) score_tiles_kernel<bf16_t, 128, 2><<<g1, kTilesThreads, 0, st>>>(a);
-      else          score_tiles_kernel<bf16_t, 64, 2><<<g1, kTilesThreads, 0, st>>>(a);
-    } else {
-      if (d == 128) score_tiles_kernel<float, 128, 2><<<g1, kTilesThreads, 0, st>>>(a);
-      else          score_tiles_kernel<float, 64, 2><<<g1, kTilesThreads, 0, st>>>(a);
-    }
-  } else {
-    const dim3 g1(a.n_tiles * a.row_chunks, a.Hkv, a.B);
-    if (bf16) {
-      if (d == 128) score_tiles_kernel<bf16_t, 128, 1><<<g1, kTilesThreads, 0, st>>>(a);
-      else          score_tiles_kernel<bf16_t, 64, 1><<<g1, kTilesThreads, 0, st>>>(a);
-    } else {
-      if (d == 128) score_tiles_kernel<float, 128, 1><<<g1, kTilesThreads, 0, st>>>(a);
-      else          score_tiles_kernel<float, 64, 1><<<g1, kTilesThreads, 0, st>>>(a);
-    }
-  }
-  hipError_t err = hipGetLastError();
+  hipError_t err = bf16 ? launch_score_tiles_bf16(a, d, st) : launch_tiles_f32(a, d, st);
   if (err != hipSuccess) return err;
-  const int waves = a.B * a.Hkv * a.R;
-  row_stats_kernel<<<(waves + 3) / 4, kThreads, 0, st>>>(a);
+  row_stats_kernel<<<dim3((a.R + kStatRows - 1) / kStatRows, a.Hkv, a.B), kStatThreads, 0, st>>>(a);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   const dim3 g3((a.Lmax + kT - 1) / kT, a.Hkv, a.B);

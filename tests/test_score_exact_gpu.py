@@ -1,0 +1,81 @@
+"""bf16 window scores at the edges of the digit kernel: row counts on both
+sides of every wave and chunk boundary, prompts around the 64-key tiles, and
+values the digits can and cannot hold (float64 products), against float64."""
+import math
+
+import pytest
+import torch
+
+from paper_2512_21859_amd import _lib
+from paper_2512_21859_amd.pipeline import Evictor
+
+pytestmark = pytest.mark.gpu
+
+# fp32 exponential (1 ulp of the hardware exp2 + half an ulp of its argument),
+# its fp32 sum of four, and the fp32 rounding of the score: under 5 * 2^-24
+REL = 3e-7
+
+
+def _values(kind, shape, g):
+    x = torch.randn(shape, generator=g)
+    if kind == "outlier":            # one channel far above the rest, as attention keys have
+        x[..., 3] *= 300.0
+    elif kind == "wide":             # magnitudes over 2^-40 .. 1: below every digit of the row
+        x = torch.sign(x) * torch.exp2(-40.0 * torch.rand(shape, generator=g)) * 8
+    elif kind == "mixed":            # some tiles only
+        x[..., 64:128, 0] = 2.0 ** -30
+        x[..., 128:192, :] = 0.0
+    elif kind == "tiny":             # bf16 subnormals among them
+        x = x * 2.0 ** -127
+    return x.to(torch.bfloat16)
+
+
+def _raw64(q, k, L, w, scale):
+    """Column sums of the window softmax in float64."""
+    B, Hq, _, d = q.shape
+    Hkv = k.shape[1]
+    G = Hq // Hkv
+    out = torch.zeros((B, Hkv, k.shape[2]), dtype=torch.float64)
+    for b, n in enumerate(L):
+        at = torch.arange(n - w, n)
+        for h in range(Hq):
+            s = q[b, h].double() @ k[b, h // G, :n].double().T * scale
+            s.masked_fill_(torch.arange(n)[None, :] > at[:, None], -math.inf)
+            out[b, h // G, :n - w] += torch.softmax(s, dim=-1).sum(dim=0)[:n - w]
+    return out
+
+
+@pytest.mark.parametrize("kind", ["normal", "outlier", "wide", "mixed", "tiny"])
+@pytest.mark.parametrize("G,w,d,L", [
+    (1, 1, 128, [65, 2, 64]), (1, 32, 64, [129, 33]), (1, 33, 128, [200]), (3, 32, 64, [777]),
+    (4, 32, 128, [63, 512]), (5, 32, 128, [300]), (7, 32, 128, [1024, 999]), (7, 32, 64, [321]),
+    (8, 32, 128, [450, 64]), (7, 40, 128, [257]), (8, 128, 64, [193]),
+])
+def test_raw_scores(kind, G, w, d, L):
+    g = torch.Generator().manual_seed(len(L) * 1000 + G * 100 + w + d)
+    B, Hkv, Lmax = len(L), 2, max(L) + 5
+    q = _values(kind if kind in ("wide", "normal") else "normal", (B, G * Hkv, w, d), g)
+    k = _values(kind, (B, Hkv, Lmax, d), g)
+    ref = _raw64(q, k, L, w, 1.0 / math.sqrt(d))
+    ev = Evictor(B, Lmax, G * Hkv, Hkv, d, w, 1)
+    ev.scores.zero_()
+    ev.score(q.cuda(), k.cuda(), L)
+    got = ev.scores.cpu().double()
+    for b, n in enumerate(L):
+        err = (got[b, :, :n - w] - ref[b, :, :n - w]).abs() / ref[b, :, :n - w].clamp_min(1e-37)
+        assert float(err.max()) <= REL, (b, float(err.max()))
+
+
+def test_not_finite():
+    """A NaN or infinite key spoils its own column only by the row sums: the
+    other tiles are still computed, and no score is left unwritten."""
+    g = torch.Generator().manual_seed(5)
+    q, k = _values("normal", (1, 4, 16, 128), g), _values("normal", (1, 1, 300, 128), g)
+    k[0, 0, 70, 5] = float("nan")
+    ev = Evictor(1, 300, 4, 1, 128, 16, 1)
+    ev.scores.fill_(-1.0)
+    ev.score(q.cuda(), k.cuda(), [300])
+    s = ev.scores[0, 0, :284].cpu()
+    assert torch.isnan(s[70])
+    s[70] = 0.0
+    assert torch.equal(s, torch.zeros_like(s))
