@@ -296,6 +296,61 @@ struct StreamTile {
   }
 };
 
+// Staging of streamed tiles by the WAVES waves of a block: wave w converts
+// groups w MP .. w MP + MP - 1.  4 or 8 waves: two LDS buffers (one barrier a
+// tile) and rows fetched a tile ahead, into registers; 1 or 2 waves: one
+// buffer, the other blocks of the CU fill the gaps.
+template <int D, int WAVES>
+struct Stager {
+  using Tile = StreamTile<D>;
+  static constexpr int MP = Tile::NG > WAVES ? Tile::NG / WAVES : 1;   // groups per wave
+  static constexpr bool kTwo = WAVES >= 4;
+  static constexpr int kBuffers = kTwo ? 2 : 1;
+  static constexpr int kWin = MP < 4 ? MP : 4;                         // groups held in registers
+  const uint16_t* src;                       // row 0
+  int n_rows, n_tiles, wave, lane;
+  uint4 raw[kWin];
+
+  __device__ __forceinline__ bool stages() const { return wave * MP < Tile::NG; }   // wave-uniform
+  // this lane's 8 elements of group u; rows past the end: the last row, tiles
+  // past the end: the last tile (a wave-uniform base and a 32-bit lane offset)
+  __device__ __forceinline__ uint4 fetch(int tile, int u) const {
+    const int k0 = min(tile, n_tiles - 1) * 64;
+    const int r = min((wave * MP + u) * Tile::RPG + lane / Tile::LPR, n_rows - 1 - k0);
+    const uint32_t off = (r * D + 8 * (lane % Tile::LPR)) * 2;
+    return ldg16(reinterpret_cast<const char*>(src + static_cast<size_t>(k0) * D) + off);
+  }
+  __device__ __forceinline__ void start(int tile) {
+    if (kTwo && stages()) {
+#pragma unroll
+      for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile, u);
+    }
+  }
+  // Stage a tile and wait for it.  Every wave of the block calls this for the
+  // same tiles from `first` on, so they meet the same barriers.
+  __device__ __forceinline__ Tile& stage(Tile* buf, int tile, int first) {
+    Tile& st = buf[kTwo ? (tile - first) & 1 : 0];
+    if (!kTwo && tile > first) __syncthreads();             // the previous tile has been read
+    if (stages()) {
+      uint32_t flags = 0u;
+#pragma unroll
+      for (int u0 = 0; u0 < MP; u0 += kWin) {
+        if (!kTwo) {
+#pragma unroll
+          for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile, u0 + u);
+        }
+#pragma unroll
+        for (int u = 0; u < kWin; ++u) flags |= st.put(wave * MP + u0 + u, lane, raw[u]);
+      }
+      if (__builtin_amdgcn_ballot_w64(flags != 0u))         // rare: the groups get their bounds
+        for (int u = 0; u < MP; ++u) st.put_bound(wave * MP + u, lane, fetch(tile, u));
+      if (kTwo) start(tile + 1);
+    }
+    __syncthreads();
+    return st;
+  }
+};
+
 // The 13 digit products of 16 streamed rows (operands A of StreamTile::get)
 // with column tile c: lane (q4, r16) gets S_s of streamed rows 4 q4 + i (item
 // i), stationary row r16 of the tile.

@@ -57,15 +57,18 @@ struct H2oArgs {
   const void* q;          // [B][Hq][Lmax][d]  all prompt queries
   const void* k;          // [B][Hkv][Lmax][d]
   float* scores;          // [B][Hkv][Lmax]: accumulated attention for j < L[b]
-  double* row_M;          // ws: [B][Hq][Lmax] row max (logit units)
-  double* row_Z;          // ws: [B][Hq][Lmax] row normaliser
+  double* row_M;          // ws: [B][Hq][Lmax] fp32: row max (logit units);
+                          //     bf16: row log-sum-exp (base 2)
+  double* row_Z;          // ws: [B][Hq][Lmax] fp32: row normaliser
   double* col_part;       // ws: [B][Hq][Lmax] per-head column mass
   int32_t B, Lmax, Hq, Hkv;
+  int32_t n_ranks;        // set by launch_h2o_passes_bf16: row (key) blocks of the longest sequence
   double scale;           // 1/sqrt(d)
   int32_t L[kMaxB];
 };
 size_t h2o_ws_bytes(int B, int Lmax, int Hq);
 hipError_t launch_h2o(const H2oArgs& a, int d, bool bf16, hipStream_t st);
+hipError_t launch_h2o_passes_bf16(const H2oArgs& a, int d, hipStream_t st);   // all but the merge
 
 // ---------------------------------------------------------------- prefill
 struct PrefillArgs {

@@ -6,9 +6,11 @@
 //   A[g][j] = sum_{h in group g} sum_{i >= j} exp(s_hij - M_hi) / Z_hi,
 //   s_hij = q[h][i] . k[g][j] / sqrt(d),  M_hi, Z_hi = max and sum of row i.
 //
-// Two passes over the causal (row tile, key tile) pairs, both on the float64
-// matrix cores (v_mfma_f64_16x16x4_f64), since the selection compares scores
-// within 1e-6 relative:
+// Two passes over the causal (row tile, key tile) pairs and a merge.  The
+// selection compares scores within 1e-6 relative, so the products are exact or
+// float64: bf16 inputs go through exact int8 digit products
+// (score_h2o_bf16.hip), fp32 inputs through the float64 matrix cores
+// (v_mfma_f64_16x16x4_f64) here:
 //   rows: block = a pair of 64-row query tiles (p, T-1-p) of one query head, so
 //     every block covers T+1 causal tile pairs; key tiles stream through LDS;
 //     each row keeps a running (max, sum) merged tile by tile in float64;
@@ -20,25 +22,16 @@
 // evaluate 2^f (|f| <= 1/2) in fp32, as in the window scorer: on this part
 // fp64 vector work competes with the fp64 matrix work for throughput.
 
-#include "common.h"
+#include "exact_dot.h"
 #include "kernels.h"
 
 namespace tb {
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) double f64x4;
-
 constexpr int kTile = 64;          // query rows / keys per tile
 constexpr int kThreads = 256;      // 4 waves of 16 rows
 
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float* out);
-template <>
-__device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float* out) {
-  Elem<bf16_t>::widen(ldg16(p), out);
-}
-template <>
-__device__ __forceinline__ void load8<float>(const float* p, float* out) {
+__device__ __forceinline__ void load8(const float* p, float* out) {
   Elem<float>::widen(ldg16(p), out);
   Elem<float>::widen(ldg16(p + 4), out + 4);
 }
@@ -71,22 +64,22 @@ __device__ __forceinline__ float row16_max_f32(float x) {
 }
 // 2^t as fp32 for a float64 t: t = n + f, n = round(t) exact, |f| <= 1/2
 // rounded to fp32, hardware 2^f, exact scaling (tiny results flush to 0).
-__device__ __forceinline__ float exp2_split(double t) {
+__device__ __forceinline__ float exp2_clamped(double t) {
   const double n = rint(fmax(t, -300.0));
   return ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - n)), static_cast<int>(n));
 }
 
 // Stage 64 rows (row0.., valid below n_rows) of a [rows][D] matrix into LDS as
 // fp32; thread t takes row t/4, elements (t%4)*D/4 ..; invalid rows are zero.
-template <typename T, int D>
-__device__ __forceinline__ void stage_tile(float (*dst)[D + 1], const T* src, int row0, int n_rows) {
+template <int D>
+__device__ __forceinline__ void stage_tile(float (*dst)[D + 1], const float* src, int row0, int n_rows) {
   constexpr int PER = D / 4;
   const int r = threadIdx.x >> 2, c0 = (threadIdx.x & 3) * PER;
   float v[PER];
   if (row0 + r < n_rows) {
-    const T* p = src + static_cast<size_t>(row0 + r) * D + c0;
+    const float* p = src + static_cast<size_t>(row0 + r) * D + c0;
 #pragma unroll
-    for (int e = 0; e < PER; e += 8) load8<T>(p + e, v + e);
+    for (int e = 0; e < PER; e += 8) load8(p + e, v + e);
   } else {
 #pragma unroll
     for (int e = 0; e < PER; ++e) v[e] = 0.f;
@@ -133,7 +126,7 @@ __device__ __forceinline__ bool h2o_block(const H2oArgs& a, int& p, int& h, int&
   return p < (nt_max + 1) / 2;
 }
 
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(kThreads, 2) void h2o_rows_kernel(H2oArgs a) {
   int p, h, b;
   if (!h2o_block(a, p, h, b)) return;
@@ -144,8 +137,8 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_rows_kernel(H2oArgs a) {
   const int q4 = lane >> 4, r16 = lane & 15;
   __shared__ float qs[kTile][D + 1];
   __shared__ float ks[kTile][D + 1];
-  const T* qh = static_cast<const T*>(a.q) + (static_cast<size_t>(b) * a.Hq + h) * a.Lmax * D;
-  const T* kg = static_cast<const T*>(a.k) + (static_cast<size_t>(b) * a.Hkv + g) * a.Lmax * D;
+  const float* qh = static_cast<const float*>(a.q) + (static_cast<size_t>(b) * a.Hq + h) * a.Lmax * D;
+  const float* kg = static_cast<const float*>(a.k) + (static_cast<size_t>(b) * a.Hkv + g) * a.Lmax * D;
   const double c = a.scale * 1.4426950408889634;
   const size_t rowbase = (static_cast<size_t>(b) * a.Hq + h) * a.Lmax;
 
@@ -153,12 +146,12 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_rows_kernel(H2oArgs a) {
     const int rt = side == 0 ? p : nt - 1 - p;
     if (rt < 0 || rt >= nt || (side == 1 && rt <= p)) continue;   // block-uniform
     __syncthreads();
-    stage_tile<T, D>(qs, qh, rt * kTile, L);
+    stage_tile<D>(qs, qh, rt * kTile, L);
     double m_run[4], z_run[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) { m_run[v] = -INFINITY; z_run[v] = 0.0; }
     for (int kt = 0; kt <= rt; ++kt) {
-      stage_tile<T, D>(ks, kg, kt * kTile, L);
+      stage_tile<D>(ks, kg, kt * kTile, L);
       __syncthreads();
       f64x4 acc[4];
       tile_products<D>(qs, ks, wave, q4, r16, acc);
@@ -177,7 +170,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_rows_kernel(H2oArgs a) {
         float zs = 0.f;
         if (md != -INFINITY) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) zs += ok[j] ? exp2_split((acc[j][v] - md) * c) : 0.f;
+          for (int j = 0; j < 4; ++j) zs += ok[j] ? exp2_clamped((acc[j][v] - md) * c) : 0.f;
         }
         const double z = row16_sum_f64(static_cast<double>(zs));
         if (md != -INFINITY) {                    // merge (md * scale, z) into the row's state
@@ -205,7 +198,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_rows_kernel(H2oArgs a) {
   }
 }
 
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(kThreads, 2) void h2o_cols_kernel(H2oArgs a) {
   int p, h, b;
   if (!h2o_block(a, p, h, b)) return;
@@ -217,8 +210,8 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_cols_kernel(H2oArgs a) {
   __shared__ float qs[kTile][D + 1];
   __shared__ float ks[kTile][D + 1];
   __shared__ double s_col[kThreads / 64][kTile];
-  const T* qh = static_cast<const T*>(a.q) + (static_cast<size_t>(b) * a.Hq + h) * a.Lmax * D;
-  const T* kg = static_cast<const T*>(a.k) + (static_cast<size_t>(b) * a.Hkv + g) * a.Lmax * D;
+  const float* qh = static_cast<const float*>(a.q) + (static_cast<size_t>(b) * a.Hq + h) * a.Lmax * D;
+  const float* kg = static_cast<const float*>(a.k) + (static_cast<size_t>(b) * a.Hkv + g) * a.Lmax * D;
   const double c = a.scale * 1.4426950408889634;
   const size_t rowbase = (static_cast<size_t>(b) * a.Hq + h) * a.Lmax;
 
@@ -226,10 +219,10 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_cols_kernel(H2oArgs a) {
     const int kt = side == 0 ? p : nt - 1 - p;
     if (kt < 0 || kt >= nt || (side == 1 && kt <= p)) continue;   // block-uniform
     __syncthreads();
-    stage_tile<T, D>(ks, kg, kt * kTile, L);
+    stage_tile<D>(ks, kg, kt * kTile, L);
     double col[4] = {0.0, 0.0, 0.0, 0.0};         // column 16 j + r16 of this key tile
     for (int rt = kt; rt < nt; ++rt) {
-      stage_tile<T, D>(qs, qh, rt * kTile, L);
+      stage_tile<D>(qs, qh, rt * kTile, L);
       __syncthreads();
       f64x4 acc[4];
       tile_products<D>(qs, ks, wave, q4, r16, acc);
@@ -245,7 +238,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_cols_kernel(H2oArgs a) {
           for (int j = 0; j < 4; ++j) {
             const int key = kt * kTile + 16 * j + r16;
             if (key <= row && key < L)
-              part[j] += static_cast<double>(exp2_split(fma(acc[j][v], c, -off))) * invZ;
+              part[j] += static_cast<double>(exp2_clamped(fma(acc[j][v], c, -off))) * invZ;
           }
         }
       }
@@ -284,20 +277,16 @@ __global__ __launch_bounds__(kThreads) void h2o_merge_kernel(H2oArgs a) {
   a.scores[(static_cast<size_t>(b) * a.Hkv + g) * a.Lmax + j] = static_cast<float>(s);
 }
 
-template <typename T, int D>
-hipError_t launch_typed(const H2oArgs& a, hipStream_t st) {
+template <int D>
+hipError_t launch_passes_f32(const H2oArgs& a, hipStream_t st) {
   int nt_max = 0;
   for (int b = 0; b < a.B; ++b) nt_max = max(nt_max, (a.L[b] + kTile - 1) / kTile);
   const int units = (nt_max + 1) / 2 * a.B * a.Hkv;          // (tile pair, batch, KV head)
   const dim3 grid(((units + 7) / 8) * 8 * (a.Hq / a.Hkv));
-  h2o_rows_kernel<T, D><<<grid, kThreads, 0, st>>>(a);
-  hipError_t e = hipGetLastError();
+  h2o_rows_kernel<D><<<grid, kThreads, 0, st>>>(a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  h2o_cols_kernel<T, D><<<grid, kThreads, 0, st>>>(a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const dim3 g3((a.Lmax + kThreads - 1) / kThreads, a.Hkv, a.B);
-  h2o_merge_kernel<<<g3, kThreads, 0, st>>>(a);
+  h2o_cols_kernel<D><<<grid, kThreads, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -309,8 +298,12 @@ size_t h2o_ws_bytes(int B, int Lmax, int Hq) {
 }
 
 hipError_t launch_h2o(const H2oArgs& a, int d, bool bf16, hipStream_t st) {
-  if (bf16) return d == 128 ? launch_typed<bf16_t, 128>(a, st) : launch_typed<bf16_t, 64>(a, st);
-  return d == 128 ? launch_typed<float, 128>(a, st) : launch_typed<float, 64>(a, st);
+  const hipError_t e = bf16 ? launch_h2o_passes_bf16(a, d, st)
+                       : d == 128 ? launch_passes_f32<128>(a, st) : launch_passes_f32<64>(a, st);
+  if (e != hipSuccess) return e;
+  const dim3 g3((a.Lmax + kThreads - 1) / kThreads, a.Hkv, a.B);
+  h2o_merge_kernel<<<g3, kThreads, 0, st>>>(a);
+  return hipGetLastError();
 }
 
 }  // namespace tb

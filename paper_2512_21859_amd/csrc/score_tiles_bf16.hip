@@ -36,9 +36,6 @@ template <int D, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
 void score_tiles_i8_kernel(ScoreArgs a) {
   using Tile = StreamTile<D>;
-  constexpr int MP = Tile::NG > WAVES ? Tile::NG / WAVES : 1;   // staging groups per wave
-  constexpr bool kTwo = WAVES >= 4;          // two LDS buffers and keys fetched a tile ahead
-  constexpr int kWin = MP < 4 ? MP : 4;      // groups held in registers
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q4 = lane >> 4, r16 = lane & 15;
@@ -56,23 +53,9 @@ void score_tiles_i8_kernel(ScoreArgs a) {
   const uint16_t* kg = static_cast<const uint16_t*>(a.k) + bg * a.Lmax * D;
   const bool active = row0 < R;              // wave-uniform
 
-  __shared__ Tile s_tile[kTwo ? 2 : 1];
-
-  // this wave's staging groups are wave * MP + u; rows past the prompt: any
-  // valid row (masked)
-  const bool stager = wave * MP < Tile::NG;  // wave-uniform
-  uint4 raw[kWin];
-  // (addresses: a wave-uniform base and a 32-bit lane offset, here and below)
-  auto fetch = [&](int tile, int u) {
-    const int k0 = min(tile, nt - 1) * kT;
-    const int key = min((wave * MP + u) * Tile::RPG + lane / Tile::LPR, L - 1 - k0);
-    uint32_t off = (key * D + 8 * (lane % Tile::LPR)) * 2;
-    return ldg16(reinterpret_cast<const char*>(kg + static_cast<size_t>(k0) * D) + off);
-  };
-  if (kTwo && stager) {
-#pragma unroll
-    for (int u = 0; u < kWin; ++u) raw[u] = fetch(t_lo, u);
-  }
+  __shared__ Tile s_tile[Stager<D, WAVES>::kBuffers];
+  Stager<D, WAVES> keys{kg, L, nt, wave, lane};
+  keys.start(t_lo);
 
   Stationary<D> sx;
   int row[2];                                // padding rows repeat row R - 1
@@ -92,40 +75,14 @@ void score_tiles_i8_kernel(ScoreArgs a) {
   const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
   const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
 
-  // stage a tile and wait for it; the waves of a block call this for the same
-  // tiles, so they meet the same barriers
-  auto stage = [&](int tile) -> Tile& {
-    Tile& st = s_tile[kTwo ? (tile - t_lo) & 1 : 0];
-    if (!kTwo && tile > t_lo) __syncthreads();              // the previous tile has been read
-    if (stager) {
-      uint32_t flags = 0u;
-#pragma unroll
-      for (int u0 = 0; u0 < MP; u0 += kWin) {
-        if (!kTwo) {
-#pragma unroll
-          for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile, u0 + u);
-        }
-#pragma unroll
-        for (int u = 0; u < kWin; ++u) flags |= st.put(wave * MP + u0 + u, lane, raw[u]);
-      }
-      if (__builtin_amdgcn_ballot_w64(flags != 0u))         // rare: the groups get their bounds
-        for (int u = 0; u < MP; ++u) st.put_bound(wave * MP + u, lane, fetch(tile, u));
-      if (kTwo) {
-#pragma unroll
-        for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile + 1, u);
-      }
-    }
-    __syncthreads();
-    return st;
-  };
-  if (!active) {
-    for (int tile = t_lo; tile < t_hi; ++tile) stage(tile);
+  if (!active) {                             // waves without rows only stage
+    for (int tile = t_lo; tile < t_hi; ++tile) keys.stage(s_tile, tile, t_lo);
     return;
   }
 
   int ref[2] = {0, 0};                       // of this lane's rows, base-2 units
   for (int tile = t_lo; tile < t_hi; ++tile) {
-    Tile& st = stage(tile);
+    Tile& st = keys.stage(s_tile, tile, t_lo);
     const int kbase = tile * kT;
     const bool edge = kbase + kT > L - w;                   // some rows do not see all 64 keys
     int lim[2] = {63, 63};                                  // last key the rows see

@@ -1,6 +1,7 @@
-"""bf16 window scores at the edges of the digit kernel: row counts on both
-sides of every wave and chunk boundary, prompts around the 64-key tiles, and
-values the digits can and cannot hold (float64 products), against float64."""
+"""bf16 window and H2O scores at the edges of the digit kernels: row counts on
+both sides of every wave, block and chunk boundary, prompts around the 64-key
+tiles, and values the digits can and cannot hold (float64 products), against
+float64."""
 import math
 
 import pytest
@@ -79,3 +80,30 @@ def test_not_finite():
     assert torch.isnan(s[70])
     s[70] = 0.0
     assert torch.equal(s, torch.zeros_like(s))
+
+
+@pytest.mark.parametrize("kind", ["normal", "outlier", "wide", "mixed", "tiny"])
+@pytest.mark.parametrize("Hq,Hkv,d,L", [
+    (2, 2, 128, [1, 64, 65]), (6, 2, 64, [127, 129, 16]), (4, 1, 128, [257, 300]),
+    (28, 4, 128, [700]), (64, 8, 64, [1030, 520]),
+])
+def test_h2o_scores(kind, Hq, Hkv, d, L):
+    g = torch.Generator().manual_seed(Hq * 1000 + d + max(L))
+    B, Lmax = len(L), max(L) + 3
+    q = _values("wide" if kind == "wide" else "normal", (B, Hq, Lmax, d), g)
+    k = _values(kind, (B, Hkv, Lmax, d), g)
+    ev = Evictor(B, Lmax, Hq, Hkv, d, 1, 1, scorer="h2o")
+    ev.scores.fill_(-1.0)
+    ev.score(q.cuda(), k.cuda(), L)
+    got = ev.scores.cpu().double()
+    for b, n in enumerate(L):
+        ref = torch.zeros((Hkv, n), dtype=torch.float64)
+        for h in range(Hq):
+            s = q[b, h, :n].double() @ k[b, h // (Hq // Hkv), :n].double().T / math.sqrt(d)
+            s.masked_fill_(torch.ones(n, n, dtype=torch.bool).triu(1), -math.inf)
+            ref[h // (Hq // Hkv)] += torch.softmax(s, dim=-1).sum(dim=0)
+        # terms under 2^-126 are fp32 subnormals, each within 2^-150: a sum of
+        # up to 4 * 1030 * 8 of them is REL-exact from 1e-35 on
+        err = (got[b, :, :n] - ref).abs() / ref.clamp_min(1e-35)
+        assert float(err.max()) <= REL, (b, float(err.max()))
+        assert bool((got[b, :, n:] == -1.0).all())
