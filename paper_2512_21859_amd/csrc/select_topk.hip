@@ -14,17 +14,14 @@
 //      key tau of the n_sel-th largest score and how many tau-valued positions
 //      to take (histogram bins are replicated per lane group to spread
 //      same-bin atomics over LDS banks);
-//   2. an ordered emit walks the prefix in tiles of 16384 positions (16 per
-//      thread, contiguous), with one block-wide exclusive scan of the packed
-//      counts (greater-than-tau, equal-to-tau) per tile.  Positions equal to
-//      tau are taken lowest index first, so a thread's output offset is
-//      (#greater before it) + min(#equal before it, equal-needed).
-// A prefix of up to 32768 positions is read from HBM once and kept in LDS for
-// every pass; a longer one is re-read (from L2) by each pass and staged
-// through the same LDS buffer one emit tile at a time.  Given a workspace,
-// longer prefixes are instead split over up to 32 blocks per KV head (the
-// second half of this file): one block per head is then 3-4x slower, since a
-// single CU streams every pass.
+//   2. an ordered emit: positions equal to tau are taken lowest index first, so
+//      a position's output offset is (#greater before it) + min(#equal before
+//      it, equal-needed).
+// Prefixes of up to 32768 positions are read once and kept in registers
+// (select_regs_kernel).  Longer ones, given a workspace, are split over up to
+// 32 blocks per KV head (the last part of this file); without one a single
+// block re-reads them (from L2) in each pass and stages the emit in LDS one
+// 16384-position tile at a time, 3-4x slower (select_long_kernel).
 
 #include "common.h"
 #include "kernels.h"
@@ -38,7 +35,6 @@ constexpr int kBits = 11;
 constexpr int kBins = 1 << kBits;
 constexpr int kPer = 16;                      // positions per thread per emit tile
 constexpr int kTileN = kThreads * kPer;       // 16384
-constexpr int kCacheN = 32768;                // prefix kept in LDS when it fits
 
 __device__ __forceinline__ uint32_t key_of(float f) {
   uint32_t u = __float_as_uint(f);
@@ -113,14 +109,13 @@ __device__ __forceinline__ void for_each_key(int n, Load load, F f) {
   }
 }
 
-// LDS slot of prefix key j (of the cached prefix or of an emit tile): the low
-// 4 bits are XORed with bits 6..9, so the emit's reads (thread t takes keys
-// 16 t .. 16 t + 15) hit 64 different banks across a wave, while the
-// counting passes' reads (64 consecutive keys per wave) stay conflict-free.
+// LDS slot of key j of an emit tile: the low 4 bits are XORed with bits 6..9,
+// so the emit's reads (thread t takes keys 16 t .. 16 t + 15) hit 64 different
+// banks across a wave.
 __device__ __forceinline__ int kslot(int j) { return j ^ ((j >> 6) & 15); }
 
-template <bool CACHED>
-__global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
+// Any prefix length, re-read by every pass (long prefixes without a workspace).
+__global__ __launch_bounds__(kThreads) void select_long_kernel(SelectArgs a) {
   const int g = blockIdx.x, b = blockIdx.y;
   const int L = a.L[b], w = a.w, pref = L - w;
   const int n_sel = a.n_keep[b] - w;
@@ -131,8 +126,8 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
 
   // Each bin has kRep interleaved copies (lane % kRep picks one), so lanes of a
   // wave that hit the same bin mostly update different LDS banks.
-  constexpr int kRep = CACHED ? 2 : 8;
-  __shared__ uint32_t s_keys[CACHED ? kCacheN : kTileN];   // the prefix, or one emit tile
+  constexpr int kRep = 8;
+  __shared__ uint32_t s_keys[kTileN];         // one emit tile
   __shared__ uint32_t hist[kBins * kRep];
   __shared__ uint32_t s_wave[2 * kWaves + 1];
   __shared__ uint32_t s_digit, s_rank;
@@ -144,12 +139,10 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
     return;
   }
 
-  // 0. key range (and the LDS copy of the prefix)
+  // 0. key range
   const auto from_hbm = [&](int j) { return key_of(sc[j]); };
-  const auto from_lds = [&](int j) { return s_keys[kslot(j)]; };
   uint32_t kmax = 0u, kmin = 0xffffffffu;
-  for_each_key(pref, from_hbm, [&](int j, uint32_t k) {
-    if (CACHED) s_keys[kslot(j)] = k;
+  for_each_key(pref, from_hbm, [&](int, uint32_t k) {
     kmax = max(kmax, k);
     kmin = min(kmin, k);
   });
@@ -172,8 +165,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
     const auto count = [&](int, uint32_t k) {
       if ((k & mask) == prefix) atomicAdd(&hist[((k >> shift) & dmask) * kRep + rep], 1u);
     };
-    if (CACHED) for_each_key(pref, from_lds, count);
-    else        for_each_key(pref, from_hbm, count);
+    for_each_key(pref, from_hbm, count);
     __syncthreads();
     // thread t holds bins kBins-1-2t and kBins-2-2t (descending digit order)
     uint32_t c0 = 0u, c1 = 0u;
@@ -201,19 +193,16 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   // 2. ordered emit.
   uint32_t gt_run = 0u, eq_run = 0u;
   for (int base = 0; base < pref; base += kTileN) {
-    const uint32_t* tk = s_keys + (CACHED ? base : 0);
-    if (!CACHED) {
-      for_each_key(min(kTileN, pref - base), [&](int i) { return key_of(sc[base + i]); },
-                   [&](int i, uint32_t k) { s_keys[kslot(i)] = k; });
-      __syncthreads();
-    }
+    for_each_key(min(kTileN, pref - base), [&](int i) { return key_of(sc[base + i]); },
+                 [&](int i, uint32_t k) { s_keys[kslot(i)] = k; });
+    __syncthreads();
     const int j0 = base + tid * kPer;
     uint32_t gt = 0u, eq = 0u, kk[kPer];
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int j = j0 + q;
       const bool in = j < pref;
-      kk[q] = in ? tk[kslot(tid * kPer + q)] : 0u;
+      kk[q] = in ? s_keys[kslot(tid * kPer + q)] : 0u;
       gt += (in && kk[q] > tau) ? 1u : 0u;
       eq += (in && kk[q] == tau) ? 1u : 0u;
     }
@@ -235,6 +224,217 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
     gt_run += total & 0xffffu;
     eq_run += total >> 16;
   }
+}
+
+// ------------------------------------------------------ keys in registers
+//
+// Prefixes of up to 4096 KJ positions (KJ <= 8): wave v holds positions
+// [256 KJ v, 256 KJ (v + 1)) in registers, lane l the four from 256 j + 4 l on
+// for j = 0 .. KJ - 1, so loads are whole lines and the ordered emit ranks a
+// wave's 256 positions of a j with ballots.  The kept positions are collected
+// in LDS and leave in whole lines (a thread storing its own run of positions
+// touches one line per lane and store: half the time of a 32768 prefix).  One
+// 11-bit radix pass usually leaves a bin of at most kFew keys; those are
+// gathered and ranked directly, in place of two more passes.
+// Bound by the chain of block barriers and LDS round trips of one CU per KV
+// head: 8192 positions 11.0 us (traced) against 15.7 with the keys in LDS,
+// three passes and scattered stores; 32768 20.9 against 29.5.
+constexpr int kFew = 256;                     // a thread per key, each reads all
+
+template <int KJ>
+__global__ __launch_bounds__(kThreads) void select_regs_kernel(SelectArgs a) {
+  const int g = blockIdx.x, b = blockIdx.y;
+  const int L = a.L[b], w = a.w, pref = L - w;
+  const int n_sel = a.n_keep[b] - w;
+  const size_t bg = static_cast<size_t>(b) * a.Hkv + g;
+  const float* sc = a.scores + bg * a.Lmax;
+  int32_t* out = a.keep_idx + bg * a.Lmax;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+  constexpr int kRep = KJ > 4 ? 2 : 4;        // interleaved copies of each bin
+  __shared__ int32_t s_out[4096 * KJ];
+  __shared__ uint32_t hist[kBins * kRep];
+  __shared__ uint32_t s_few[kFew];
+  __shared__ uint32_t s_wave[2 * kWaves + 1];
+  __shared__ uint32_t s_digit, s_rank, s_count, s_n;
+
+  for (int i = tid; i < w; i += kThreads) out[n_sel + i] = pref + i;
+  if (n_sel <= 0) return;
+  if (n_sel >= pref) {
+    for (int j = tid; j < pref; j += kThreads) out[j] = j;
+    return;
+  }
+
+  // 0. the keys and their range; positions past the prefix get key 0, which
+  // no finite score has and which sorts last
+  const int p0 = wave * 256 * KJ + 4 * lane;
+  const bool full = (wave + 1) * 256 * KJ <= pref;          // wave-uniform: all positions count
+  uint32_t key[KJ][4];
+  if (reinterpret_cast<uintptr_t>(sc) % 16 == 0) {          // block-uniform
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      const int p = p0 + 256 * j;
+      uint4 v = {0u, 0u, 0u, 0u};
+      if (p + 3 < a.Lmax) v = ldg16(sc + p);
+      else {
+        uint32_t* x = &v.x;
+        for (int q = 0; q < 4; ++q) if (p + q < a.Lmax) x[q] = __float_as_uint(sc[p + q]);
+      }
+      key[j][0] = v.x; key[j][1] = v.y; key[j][2] = v.z; key[j][3] = v.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) key[j][q] = __float_as_uint(sc[min(p0 + 256 * j + q, a.Lmax - 1)]);
+  }
+  for (int i = tid; i < kBins * kRep; i += kThreads) hist[i] = 0u;
+  if (tid == 0) s_n = 0u;
+  uint32_t kmax = 0u, kmin = 0xffffffffu;
+#pragma unroll
+  for (int j = 0; j < KJ; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool in = p0 + 256 * j + q < pref;
+      const uint32_t k = key_of(__uint_as_float(key[j][q]));
+      key[j][q] = in ? k : 0u;
+      kmax = max(kmax, key[j][q]);
+      kmin = min(kmin, in ? k : 0xffffffffu);
+    }
+  block_max_min(kmax, kmin, s_wave);          // ends with a barrier
+  const uint32_t diff = kmax ^ kmin;
+  int lo = diff ? 32 - __clz(diff) : 1;       // bits [0, lo) still to resolve
+  uint32_t mask = lo >= 32 ? 0u : ~((1u << lo) - 1u);
+  uint32_t prefix = kmax & mask;
+  uint32_t rank = static_cast<uint32_t>(n_sel);
+
+  // 1. the rank-th largest key among those matching prefix
+  for (bool first = true; lo > 0; first = false) {
+    const int shift = max(lo - kBits, 0);
+    const uint32_t dmask = (1u << (lo - shift)) - 1u;
+    if (!first) {
+      for (int i = tid; i < kBins * kRep; i += kThreads) hist[i] = 0u;
+      __syncthreads();
+    }
+    const uint32_t rep = tid % kRep;
+    if (first && full) {                      // every key shares the common bits
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) atomicAdd(&hist[((key[j][q] >> shift) & dmask) * kRep + rep], 1u);
+    } else {
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (p0 + 256 * j + q < pref && (key[j][q] & mask) == prefix)
+            atomicAdd(&hist[((key[j][q] >> shift) & dmask) * kRep + rep], 1u);
+    }
+    __syncthreads();
+    // thread t holds bins kBins-1-2t and kBins-2-2t (descending digit order)
+    uint32_t c0 = 0u, c1 = 0u;
+#pragma unroll
+    for (int r = 0; r < kRep; ++r) {
+      c0 += hist[(kBins - 1 - 2 * tid) * kRep + r];
+      c1 += hist[(kBins - 2 - 2 * tid) * kRep + r];
+    }
+    uint32_t total;
+    const uint32_t ex = block_exclusive_scan(c0 + c1, s_wave, total);
+    if (ex < rank && rank <= ex + c0 + c1) {
+      if (ex + c0 >= rank) { s_digit = kBins - 1 - 2 * tid; s_rank = rank - ex; s_count = c0; }
+      else                 { s_digit = kBins - 2 - 2 * tid; s_rank = rank - ex - c0; s_count = c1; }
+    }
+    __syncthreads();
+    prefix |= s_digit << shift;
+    mask |= dmask << shift;
+    rank = s_rank;
+    lo = shift;
+    const uint32_t count = s_count;
+    if (lo > 0 && count <= kFew) {            // block-uniform: gather and rank
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (p0 + 256 * j + q < pref && (key[j][q] & mask) == prefix) s_few[atomicAdd(&s_n, 1u)] = key[j][q];
+      __syncthreads();
+      if (tid < static_cast<int>(count)) {
+        const uint32_t mine = s_few[tid];
+        uint32_t gt = 0u, eq = 0u;
+        for (uint32_t i = 0; i < count; ++i) {
+          gt += s_few[i] > mine ? 1u : 0u;
+          eq += s_few[i] == mine ? 1u : 0u;
+        }
+        if (gt < rank && rank <= gt + eq) { s_digit = mine; s_rank = rank - gt; }   // equal keys: one value
+      }
+      __syncthreads();
+      prefix = s_digit;
+      rank = s_rank;
+      lo = 0;
+    }
+    __syncthreads();
+  }
+  const uint32_t tau = prefix;
+  const uint32_t need_eq = rank;              // tau-valued positions to keep
+
+  // 2. ordered emit: counts of the wave, offsets of the waves, positions.
+  // (With tau = 0, which only scores that are not finite give, the key 0 of a
+  // position past the prefix must not count as equal to it.)
+  uint32_t gt = 0u, eq = 0u;
+#pragma unroll
+  for (int j = 0; j < KJ; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (!full && p0 + 256 * j + q >= pref && tau == 0u) continue;
+      gt += key[j][q] > tau ? 1u : 0u;
+      eq += key[j][q] == tau ? 1u : 0u;
+    }
+  // a wave's counts are at most 2048: both fit one word
+  uint32_t both = gt | (eq << 16);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) both += __shfl_xor(both, off);
+  if (lane == 0) s_wave[wave] = both;
+  __syncthreads();
+  uint32_t gs = 0u, es = 0u;                  // before this wave
+  for (int i = 0; i < wave; ++i) { gs += s_wave[i] & 0xffffu; es += s_wave[i] >> 16; }
+#pragma unroll
+  for (int j = 0; j < KJ; ++j) {
+    uint32_t g0 = gs, e0 = es;                // before this lane's first position
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t m = __ballot(key[j][q] > tau);
+      g0 = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), g0));
+      gs += __popcll(m);
+    }
+    const bool any = __ballot(key[j][0] == tau || key[j][1] == tau || key[j][2] == tau || key[j][3] == tau) != 0;
+    if (any) {                                // wave-uniform; few groups hold the threshold
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t m = __ballot(key[j][q] == tau && p0 + 256 * j + q < pref);
+        e0 = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), e0));
+        es += __popcll(m);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int p = p0 + 256 * j + q;
+        const bool above = key[j][q] > tau, same = key[j][q] == tau && p < pref;
+        if (above || (same && e0 < need_eq)) s_out[g0 + min(e0, need_eq)] = p;
+        g0 += above ? 1u : 0u;
+        e0 += same ? 1u : 0u;
+      }
+    } else {
+      uint32_t o = g0 + min(e0, need_eq);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool above = key[j][q] > tau;
+        if (above) s_out[o] = p0 + 256 * j + q;
+        o += above ? 1u : 0u;
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < n_sel; i += kThreads) out[i] = s_out[i];
 }
 
 // ------------------------------------------------- several blocks per KV head
@@ -539,8 +739,11 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t st) {
   const dim3 grid(a.Hkv, a.B);
   int max_pref = 0;
   for (int b = 0; b < a.B; ++b) max_pref = max(max_pref, a.L[b] - a.w);
-  if (max_pref <= kCacheN) select_kernel<true><<<grid, kThreads, 0, st>>>(a);
-  else                     select_kernel<false><<<grid, kThreads, 0, st>>>(a);
+  if (max_pref <= 4096)       select_regs_kernel<1><<<grid, kThreads, 0, st>>>(a);
+  else if (max_pref <= 8192)  select_regs_kernel<2><<<grid, kThreads, 0, st>>>(a);
+  else if (max_pref <= 16384) select_regs_kernel<4><<<grid, kThreads, 0, st>>>(a);
+  else if (max_pref <= 32768) select_regs_kernel<8><<<grid, kThreads, 0, st>>>(a);
+  else                        select_long_kernel<<<grid, kThreads, 0, st>>>(a);
   return hipGetLastError();
 }
 
