@@ -105,14 +105,19 @@ __device__ __forceinline__ float from_group0(float x, int lane) {
   return __shfl(x, lane & 15);
 }
 
-// WAVES waves of CQ column tiles each per block; K and V stages of STAGE keys
-template <int D, int CQ, int WAVES, int STAGE>
+// WAVES waves of CQ column tiles each per block; K and V stages of STAGE keys.
+// SPLIT = 2: two waves share a row tile, each taking half of every stage's
+// keys, and meet through LDS at the end (short prompts, where the heaviest
+// block's serial chain of steps is the time).
+template <int D, int CQ, int WAVES, int STAGE, int SPLIT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(CQ == 2 ? 2 : 1)))
 void prefill_attn_kernel(PrefillArgs a) {
   constexpr int kWaves = WAVES;
   constexpr int kStage = STAGE;               // keys per LDS stage
   constexpr int kRowsPerWave = 16 * CQ;       // CQ 16-query column tiles per wave
-  constexpr int kBlockRows = kWaves * kRowsPerWave;
+  constexpr int kRowWaves = kWaves / SPLIT;
+  constexpr int kBlockRows = kRowWaves * kRowsPerWave;
+  constexpr int kSteps = kStage / 32 / SPLIT; // 32-key steps of a wave per stage
   constexpr int KC = D / 32;                  // k-chunks of the QK^T product
   constexpr int NC = D / 16;                  // d-blocks of the PV product
   // Block order (one-dimensional grid): workgroup i runs on XCD i % 8, and
@@ -152,7 +157,8 @@ void prefill_attn_kernel(PrefillArgs a) {
   const uint16_t* kg = static_cast<const uint16_t*>(a.k) + bg * a.Lmax * D;
   const uint16_t* vg = static_cast<const uint16_t*>(a.v) + bg * a.Lmax * D;
 
-  const int row0 = qt * kBlockRows + wave * kRowsPerWave;     // this wave's first query
+  const int row0 = qt * kBlockRows + (wave % kRowWaves) * kRowsPerWave;   // this wave's first query
+  const int step0 = SPLIT > 1 ? wave / kRowWaves * kSteps : 0;            // its first step of a stage
   // Q^T operands: column tile cq, lane holds query row0 + 16 cq + r16, d = 32 kc + 8 q4 .. +8
   u32x4 qB[CQ][KC];
 #pragma unroll
@@ -194,6 +200,14 @@ void prefill_attn_kernel(PrefillArgs a) {
   const uint32_t one2 = r16 == 0 ? 0x3F803F80u : 0u;          // two bf16 ones
   const u32x4 onesA = {one2, one2, one2, one2};
   const int krow0 = 8 * (r16 >> 2) + (r16 & 3);                // permuted K row of MFMA row r16
+  // byte offsets of this lane's V^T reads in a stage: row 8 q4 + r16 / 4, the
+  // half chunk of d = 16 n + 4 (r16 & 3)
+  uint32_t v_lane[NC];
+#pragma unroll
+  for (int n = 0; n < NC; ++n) {
+    const int R = 8 * q4 + (r16 >> 2), cv = 2 * n + ((r16 & 3) >> 1);
+    v_lane[n] = (R * CH + (cv ^ vswz<D>(R))) * 16 + (r16 & 1) * 8;
+  }
 
   const int key_end = min(L, (qt + 1) * kBlockRows);            // causal limit of the block
   const int wave_key_end = min(L, row0 + kRowsPerWave);         // causal limit of this wave
@@ -218,10 +232,9 @@ void prefill_attn_kernel(PrefillArgs a) {
 
   auto compute_stage = [&](int s0, const u32x4 (&src)[2][SCH]) {
     const u32x4* sk = src[0];
-    const u32x4* sv = src[1];
 #pragma unroll
-    for (int sub = 0; sub < kStage / 32; ++sub) {
-      const int base = s0 + 32 * sub;                           // first key of the 32-key step
+    for (int sub = 0; sub < kSteps; ++sub) {
+      const int base = s0 + 32 * (step0 + sub);                           // first key of the 32-key step
       if (base >= wave_key_end) continue;                       // wave-uniform: all keys masked
       // K operands of the step (shared by both column tiles)
       u32x4 kA[2][KC];
@@ -229,23 +242,9 @@ void prefill_attn_kernel(PrefillArgs a) {
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) {
-          const int R = 32 * sub + krow0 + 4 * t;
+          const int R = 32 * (step0 + sub) + krow0 + 4 * t;
           kA[t][kc] = sk[R * CH + ((4 * kc + q4) ^ kswz<D>(R))];
         }
-      // V^T operands by transpose reads: lane (q4, r16) fetches d = 16 n +
-      // 4 (r16 & 3) .. +3 of keys 8 q4 + r16 / 4 (and + 4) and receives
-      // d = 16 n + r16 of keys 8 q4 .. 8 q4 + 7
-      u32x4 vA[NC];
-#pragma unroll
-      for (int n = 0; n < NC; ++n) {
-        const int R1 = 32 * sub + 8 * q4 + (r16 >> 2), R2 = R1 + 4;
-        const int cv = 2 * n + ((r16 & 3) >> 1);                // chunk of d = 16 n + 4 (r16 & 3)
-        const int half = (r16 & 1) * 4;                         // bf16 offset of that half chunk
-        const uint16_t* p1 = reinterpret_cast<const uint16_t*>(sv + R1 * CH + (cv ^ vswz<D>(R1))) + half;
-        const uint16_t* p2 = reinterpret_cast<const uint16_t*>(sv + R2 * CH + (cv ^ vswz<D>(R2))) + half;
-        const u32x2 lo = lds_read_tr16(p1), hi = lds_read_tr16(p2);
-        vA[n] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-      }
       const bool need_mask = base + 32 > row0;                  // step reaches this wave's diagonal
       // The step runs in phases over the column tiles: every tile's QK
       // products, the mask, every tile's softmax, the window statistics, one
@@ -263,6 +262,16 @@ void prefill_attn_kernel(PrefillArgs a) {
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kA[t][kc]), as_bf16x8(qB[cq][kc]), acc, 0, 0, 0);
           S[cq][t] = acc;
         }
+      // V^T operands by transpose reads: lane (q4, r16) fetches d = 16 n +
+      // 4 (r16 & 3) .. +3 of keys 8 q4 + r16 / 4 (and + 4) and receives
+      // d = 16 n + r16 of keys 8 q4 .. 8 q4 + 7
+      u32x4 vA[NC];
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        const char* p = reinterpret_cast<const char*>(src[1]) + v_lane[n] + (step0 + sub) * 64 * D;
+        const u32x2 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 8 * D);   // rows +4 share the swizzle
+        vA[n] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+      }
       // lane holds keys base + 8 q4 + j (j = 4t + i) of query row0 + 16 cq + r16
       if (need_mask) {
 #pragma unroll
@@ -344,9 +353,10 @@ void prefill_attn_kernel(PrefillArgs a) {
   // stage's loads (and for every wave to be done with the other buffer),
   // start the next stage's loads into the other buffer, compute.  (The
   // compiler cannot tell the transpose reads from the loads landing in the
-  // other buffer and makes them wait for those loads, so the overlap is the
-  // first step's K reads and QK products; still 9% faster than staging
-  // through registers, and bit-identical to it.)
+  // other buffer and makes them wait for those loads.  Transpose reads in
+  // inline asm, which do not wait, changed nothing: 1693 / 1683 us at
+  // N = 16384, 1-2% slower at 1300-2000; the direct loads are still 9% faster
+  // than staging through registers.)
   load_stage(0, s_kv0);
   for (int s0 = 0; s0 < key_end; s0 += 2 * kStage) {
     __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
@@ -358,6 +368,35 @@ void prefill_attn_kernel(PrefillArgs a) {
     __syncthreads();
     if (s0 + 2 * kStage < key_end) load_stage(s0 + 2 * kStage, s_kv0);
     compute_stage(s0 + kStage, s_kv1);
+  }
+
+  if constexpr (SPLIT > 1) {
+    // the second wave of a row tile hands its state over (a row it saw no key
+    // of has the reference -inf and weight 0)
+    static_assert(SPLIT == 2 && CQ == 1 && kRowWaves * (NC + 1) * 64 <= 2 * SCH, "hand-over fits a stage buffer");
+    f32x4* ex = reinterpret_cast<f32x4*>(&s_kv0[0][0]) + (wave % kRowWaves) * (NC + 1) * 64 + lane;
+    __syncthreads();                                            // the last stage has been read
+    if (wave >= kRowWaves) {
+#pragma unroll
+      for (int n = 0; n < NC; ++n) ex[64 * n] = accO[0][n];
+      ex[64 * NC] = f32x4{accL[0][0], m_ref[0], l_part[0], m_max[0]};
+    }
+    __syncthreads();
+    if (wave >= kRowWaves) return;
+    const f32x4 o = ex[64 * NC];
+    const float M = fmaxf(m_ref[0], o[1]);                      // finite: key 0 is this wave's
+    const float w0 = __builtin_amdgcn_exp2f((m_ref[0] - M) * a.scale_log2);
+    const float w1 = __builtin_amdgcn_exp2f((o[1] - M) * a.scale_log2);
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+      const f32x4 x = ex[64 * n];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) accO[0][n][i] = accO[0][n][i] * w0 + x[i] * w1;
+    }
+    accL[0][0] = accL[0][0] * w0 + o[0] * w1;
+    l_part[0] = l_part[0] * w0 + o[2] * w1;
+    m_ref[0] = M;
+    m_max[0] = fmax2(m_max[0], o[3]);
   }
 
   // finalize: lane holds d = 16 n + 4 q4 .. +3 of query row0 + 16 cq + r16
@@ -393,15 +432,15 @@ void prefill_attn_kernel(PrefillArgs a) {
 
 }  // namespace
 
-template <int CQ, int WAVES, int STAGE>
+template <int CQ, int WAVES, int STAGE, int SPLIT>
 hipError_t launch_prefill_cq(const PrefillArgs& a, int d, int lmax, hipStream_t st) {
-  constexpr int rows = WAVES * 16 * CQ;
+  constexpr int rows = WAVES / SPLIT * 16 * CQ;
   // units of (query tile rank, batch, KV head), padded to whole rounds of
   // the 8 XCDs, times the G query heads of each
   const int units = ((lmax + rows - 1) / rows) * a.B * a.Hkv;
   const dim3 grid(((units + 7) / 8) * 8 * (a.Hq / a.Hkv));
-  if (d == 128) prefill_attn_kernel<128, CQ, WAVES, STAGE><<<grid, 64 * WAVES, 0, st>>>(a);
-  else          prefill_attn_kernel<64, CQ, WAVES, STAGE><<<grid, 64 * WAVES, 0, st>>>(a);
+  if (d == 128) prefill_attn_kernel<128, CQ, WAVES, STAGE, SPLIT><<<grid, 64 * WAVES, 0, st>>>(a);
+  else          prefill_attn_kernel<64, CQ, WAVES, STAGE, SPLIT><<<grid, 64 * WAVES, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -420,12 +459,26 @@ hipError_t launch_prefill(const PrefillArgs& a, int d, hipStream_t st) {
   //   128-row launch has 224 blocks for 256 CUs at N = 1024 and the heaviest
   //   query tile's serial steps set the time; twice the blocks with half
   //   the work per step: 49 -> 58 at N = 256, 124 -> 144 at 512, 284 -> 301
-  //   at 1024 (at 2048 it lost 7%, at 4096 27%).
+  //   at 1024 (at 2048 it lost 7%, at 4096 27%);
+  // * where the heaviest block's chain of steps is the time (64-row blocks few
+  //   enough for about two rounds), two waves share a row tile and halve the
+  //   chain, 8 waves and 128-key stages.  us per call, without / with, 28
+  //   heads of d = 128 (one block per CU): N = 257 8.4 / 7.8, 512 12.9 / 10.8,
+  //   1001 23.9 / 22.2, but 200 7.2 / 7.4, 1300 33.2 / 33.8; 14 heads of
+  //   d = 64 (two per CU): 512 9.2 / 6.9, 1001 15.2 / 10.1, 2048 32.1 / 18.4,
+  //   4096 (896 blocks) 62.9 / 49.2, 8192 149.5 / 154.9; four sequences of
+  //   1001 (896 blocks) 16.9 / 18.8.
   int lmax = 0;
-  for (int b = 0; b < a.B; ++b) lmax = max(lmax, a.L[b]);
-  if (lmax <= 1024) return launch_prefill_cq<1, 4, 64>(a, d, lmax, st);
-  if (lmax < 8192) return launch_prefill_cq<2, 4, 64>(a, d, lmax, st);
-  return launch_prefill_cq<2, 8, 128>(a, d, lmax, st);
+  long long blocks = 0;                      // of 64 rows
+  for (int b = 0; b < a.B; ++b) {
+    lmax = max(lmax, a.L[b]);
+    blocks += static_cast<long long>((a.L[b] + 63) / 64) * a.Hq;
+  }
+  const bool chain = lmax > (d == 128 ? 256 : 192) && (lmax <= 1024 ? blocks <= 512 : d == 64 && lmax < 8192 && blocks <= 1024);
+  if (chain) return launch_prefill_cq<1, 8, 128, 2>(a, d, lmax, st);
+  if (lmax <= 1024) return launch_prefill_cq<1, 4, 64, 1>(a, d, lmax, st);
+  if (lmax < 8192) return launch_prefill_cq<2, 4, 64, 1>(a, d, lmax, st);
+  return launch_prefill_cq<2, 8, 128, 1>(a, d, lmax, st);
 }
 
 }  // namespace tb
