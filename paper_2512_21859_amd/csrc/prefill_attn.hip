@@ -120,6 +120,10 @@ void prefill_attn_kernel(PrefillArgs a) {
   constexpr int kSteps = kStage / 32 / SPLIT; // 32-key steps of a wave per stage
   constexpr int KC = D / 32;                  // k-chunks of the QK^T product
   constexpr int NC = D / 16;                  // d-blocks of the PV product
+  // The reference before a row's first step.  A split row's second wave starts
+  // behind key 0, on keys that may all be at -inf: with a finite reference
+  // their P is 0.
+  constexpr float kFirstRef = SPLIT > 1 ? -3.40282347e38f : -INFINITY;
   // Block order (one-dimensional grid): workgroup i runs on XCD i % 8, and
   // XCD x takes the units x, x + 8, x + 16, ... of (query tile rank, batch,
   // KV head), heaviest tiles first; the G query heads of a unit sit in G
@@ -191,9 +195,9 @@ void prefill_attn_kernel(PrefillArgs a) {
 #pragma unroll
     for (int n = 0; n < NC; ++n) accO[cq][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     accL[cq] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_ref[cq] = -INFINITY;
-    m_thr[cq] = -INFINITY;
-    m_sc[cq] = -INFINITY;
+    m_ref[cq] = kFirstRef;
+    m_thr[cq] = kFirstRef;
+    m_sc[cq] = kFirstRef * a.scale_log2;
     l_part[cq] = 0.f;
     m_max[cq] = -INFINITY;
   }
@@ -296,9 +300,11 @@ void prefill_attn_kernel(PrefillArgs a) {
       }
       // Each lane first compares the maximum of its own 8 keys with the
       // reference; only when some lane exceeds it by more than kLazy (always
-      // on a row's first step: m_ref = -inf there, and every wave's first
-      // step holds key 0, which no query masks) does the wave take the row
-      // maxima over the 4 lane groups and move those rows' references.
+      // on a row's first step) does the wave take the row maxima over the 4
+      // lane groups and move those rows' references.  A step that runs masks
+      // no row throughout: base is a multiple of 32 and below the wave's last
+      // row, so with one row tile per wave base <= row0, and with two (whose
+      // row0 is a multiple of 32) as well: every row sees key `base`.
       float xm[CQ];
       bool grow = false;
 #pragma unroll
@@ -324,6 +330,14 @@ void prefill_attn_kernel(PrefillArgs a) {
           l_part[cq] *= corr;
           m_ref[cq] = m_new;
           m_sc[cq] = m_new * a.scale_log2;
+          // Logits past 2^31, as keys masked with a huge finite value have,
+          // round the offset by more than P's range: then it is rounded up, so
+          // P is 0, not inf.  (A wave that holds every key of its row has an
+          // ordinary one in the reference; half of a split row may not.)
+          if constexpr (SPLIT > 1) {
+            if (fmaf(m_new, a.scale_log2, -m_sc[cq]) > 64.f)
+              m_sc[cq] = __uint_as_float(__float_as_uint(m_sc[cq]) + (m_sc[cq] < 0.f ? -1 : 1));
+          }
           m_thr[cq] = m_new + kLazy / a.scale_log2;
         }
       }
@@ -383,22 +397,23 @@ void prefill_attn_kernel(PrefillArgs a) {
   }
 
   if constexpr (SPLIT > 1) {
-    // the second wave of a row tile hands its state over (a row it saw no key
-    // of has the reference -inf and weight 0)
+    // the second wave of a row tile hands its state over, relative to the
+    // offset its P were taken with (a row it saw no key of has the first
+    // reference and sums of 0)
     static_assert(SPLIT == 2 && CQ == 1 && kRowWaves * (NC + 1) * 64 <= 2 * SCH, "hand-over fits a stage buffer");
     f32x4* ex = reinterpret_cast<f32x4*>(&s_kv0[0][0]) + (wave % kRowWaves) * (NC + 1) * 64 + lane;
     __syncthreads();                                            // the last stage has been read
     if (wave >= kRowWaves) {
 #pragma unroll
       for (int n = 0; n < NC; ++n) ex[64 * n] = accO[0][n];
-      ex[64 * NC] = f32x4{accL[0][0], m_ref[0], l_part[0], m_max[0]};
+      ex[64 * NC] = f32x4{accL[0][0], m_sc[0], l_part[0], m_max[0]};
     }
     __syncthreads();
     if (wave >= kRowWaves) return;
     const f32x4 o = ex[64 * NC];
-    const float M = fmaxf(m_ref[0], o[1]);                      // finite: key 0 is this wave's
-    const float w0 = __builtin_amdgcn_exp2f((m_ref[0] - M) * a.scale_log2);
-    const float w1 = __builtin_amdgcn_exp2f((o[1] - M) * a.scale_log2);
+    const float M = fmaxf(m_sc[0], o[1]);
+    const float w0 = __builtin_amdgcn_exp2f(m_sc[0] - M);
+    const float w1 = __builtin_amdgcn_exp2f(o[1] - M);
 #pragma unroll
     for (int n = 0; n < NC; ++n) {
       const f32x4 x = ex[64 * n];
@@ -407,7 +422,7 @@ void prefill_attn_kernel(PrefillArgs a) {
     }
     accL[0][0] = accL[0][0] * w0 + o[0] * w1;
     l_part[0] = l_part[0] * w0 + o[2] * w1;
-    m_ref[0] = M;
+    m_sc[0] = M;
     m_max[0] = fmax2(m_max[0], o[3]);
   }
 
@@ -420,7 +435,8 @@ void prefill_attn_kernel(PrefillArgs a) {
     if (stats_wave) {
       z = l_part[cq] + __shfl_xor(l_part[cq], 16);
       z += __shfl_xor(z, 32);
-      z *= __builtin_amdgcn_exp2f((m_ref[cq] - m_max[cq]) * a.scale_log2);   // to the true maximum
+      z *= __builtin_amdgcn_exp2f(SPLIT > 1 ? fmaf(-m_max[cq], a.scale_log2, m_sc[cq])   // to the true maximum
+                                            : (m_ref[cq] - m_max[cq]) * a.scale_log2);
     }
     const int qi = row0 + 16 * cq + r16;
     if (qi < L) {

@@ -18,10 +18,29 @@ pytestmark = pytest.mark.gpu
 ])
 def test_split(Hq, Hkv, d, L, w):
     g = torch.Generator().manual_seed(Hq * 100 + d + max(L))
-    B, Lmax, G = len(L), max(L) + 7, Hq // Hkv
+    B, Lmax = len(L), max(L) + 7
     q, k, v = (torch.randn((B, h, Lmax, d), generator=g).bfloat16() for h in (Hq, Hkv, Hkv))
     k[:, :, ::50] *= 4                       # heavy keys, met at any time of a row's chain
-    w = min(w, min(L))
+    _check(q, k, v, L, min(w, min(L)))
+
+
+@pytest.mark.parametrize("low", [-math.inf, float(torch.finfo(torch.bfloat16).min), -1e30])
+@pytest.mark.parametrize("first,last", [(64, 96), (64, 128), (70, 400)])
+@pytest.mark.parametrize("Hq,Hkv,d,L", [(4, 2, 64, [193, 100]), (2, 1, 128, [400]), (2, 2, 128, [200])])
+def test_masked_keys(Hq, Hkv, d, L, first, last, low):
+    """Keys that one channel takes to the lowest logits have no weight, also
+    where they are all that one wave of a row tile sees (first or throughout)."""
+    g = torch.Generator().manual_seed(Hq * 100 + d + max(L) + last)
+    B, Lmax = len(L), max(L) + 7
+    q, k, v = (torch.randn((B, h, Lmax, d), generator=g).bfloat16() for h in (Hq, Hkv, Hkv))
+    q[..., 0] = 1.0
+    k[:, :, first:last, 0] = low
+    _check(q, k, v, L, 16)
+
+
+def _check(q, k, v, L, w):
+    B, Hq, Lmax, d = q.shape
+    G = Hq // k.shape[1]
     out = torch.full((B, Hq, Lmax, d), -7.0, dtype=torch.bfloat16, device="cuda")
     stats = torch.zeros((B, Hq, w, 2), device="cuda")
     _lib.tb_prefill_attn(q.cuda(), k.cuda(), v.cuda(), L, out, w, stats)
