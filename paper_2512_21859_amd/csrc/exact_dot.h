@@ -184,6 +184,11 @@ __device__ __forceinline__ float exp2_split(double t) {
   const double n = rint(t);
   return ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - n)), static_cast<int>(n));
 }
+// the same for any t: 2^-inf = 0, and n stays within int
+__device__ __forceinline__ float exp2_clamped(double t) {
+  const double n = rint(fmax(t, -300.0));
+  return ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - n)), static_cast<int>(fmin(n, 300.0)));
+}
 
 // ------------------------------------------------------ stationary operand
 // The wave's 32 stationary rows (two 16-row column tiles) as digit planes in

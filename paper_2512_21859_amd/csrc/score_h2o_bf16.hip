@@ -29,8 +29,9 @@ namespace {
 constexpr int kT = 64;                       // streamed rows per tile
 constexpr int kNone = -(1 << 29);            // n of a masked logit
 // a reference stands while the tile's largest n is at most kHigh above it, and
-// a row's first tile's at least kLow (the row's largest term then keeps its
-// fp32 precision, and everything under 2^-102 of it vanishes)
+// that of the row's first tile with a logit over -inf at least kLow (the row's
+// largest term then keeps its fp32 precision, and everything under 2^-102 of it
+// vanishes)
 constexpr int kLow = -24, kHigh = 60;
 
 // Block order (one-dimensional grid): workgroup i runs on XCD i % 8, and XCD x
@@ -84,6 +85,7 @@ void h2o_rows_i8_kernel(H2oArgs a) {
                         static_cast<double>(sx.unit[1]) * (cd * 0x1p24)};
 
   double ref[2] = {0.0, 0.0}, z[2] = {0.0, 0.0};            // this lane's share of the sum
+  bool seen[2] = {false, false};                            // the row has had a logit over -inf
   for (int tile = 0; tile < t_hi; ++tile) {
     Tile& st = keys.stage(s_tile, tile, 0);
     if (tile >= w_hi) continue;                             // wave-uniform
@@ -96,11 +98,12 @@ void h2o_rows_i8_kernel(H2oArgs a) {
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const double to = rint(top[c]), over = to - ref[c];
-        if (fabs(top[c]) < INFINITY && (over > kHigh || (tile == 0 && over < kLow))) {
+        if (fabs(top[c]) < INFINITY && (over > kHigh || (!seen[c] && over < kLow))) {
           z[c] = ldexp(z[c], static_cast<int>(fmax(-over, -4000.0)));
           ref[c] = to;
           moved = true;
         }
+        seen[c] = seen[c] || top[c] > -INFINITY;
       }
       return __builtin_amdgcn_ballot_w64(moved) == 0;
     };
@@ -162,7 +165,7 @@ void h2o_rows_i8_kernel(H2oArgs a) {
               const double t = acc[c][i] * cd;
               const bool ok = kbase + 16 * kt + 4 * q4 + i <= row0 + 16 * c + r16;
               tops[c] = ok ? fmax(tops[c], t) : tops[c];
-              zs += ok ? exp2_split(fma(acc[c][i], cd, -ref[c])) : 0.f;
+              zs += ok ? exp2_clamped(fma(acc[c][i], cd, -ref[c])) : 0.f;
             }
             zt[c] += static_cast<double>(zs);
           }
@@ -174,7 +177,8 @@ void h2o_rows_i8_kernel(H2oArgs a) {
         }
         if (settle(tops) || round > 0) {
 #pragma unroll
-          for (int c = 0; c < 2; ++c) z[c] += zt[c];
+          for (int c = 0; c < 2; ++c)         // a tile without a logit over -inf adds nothing
+            if (tops[c] > -INFINITY) z[c] += zt[c];
           break;
         }
       }
@@ -271,7 +275,7 @@ void h2o_cols_i8_kernel(H2oArgs a) {
           for (int i = 0; i < 4; ++i) {
             const int r = rbase + 16 * kt + 4 * q4 + i;
             if (r < L && r >= key0 + 16 * c + r16)
-              sum[c] += static_cast<double>(exp2_split(fma(acc[c][i], cd, -so[16 * kt + 4 * q4 + i])));
+              sum[c] += static_cast<double>(exp2_clamped(fma(acc[c][i], cd, -so[16 * kt + 4 * q4 + i])));
           }
       }
     }

@@ -82,6 +82,19 @@ def test_not_finite():
     assert torch.equal(s, torch.zeros_like(s))
 
 
+def _h2o_ref(q, k, n):
+    """Column sums of the causal softmax of one sequence in float64 (NaN where a
+    row without a finite logit reaches)."""
+    Hq, Hkv = q.shape[0], k.shape[0]
+    ref = torch.zeros((Hkv, n), dtype=torch.float64)
+    later = torch.ones(n, n, dtype=torch.bool).triu(1)
+    for h in range(Hq):
+        s = q[h, :n].double() @ k[h // (Hq // Hkv), :n].double().T / math.sqrt(q.shape[-1])
+        s.masked_fill_(later, -math.inf)
+        ref[h // (Hq // Hkv)] += torch.softmax(s, dim=-1).masked_fill(later, 0.0).sum(dim=0)
+    return ref
+
+
 @pytest.mark.parametrize("kind", ["normal", "outlier", "wide", "mixed", "tiny"])
 @pytest.mark.parametrize("Hq,Hkv,d,L", [
     (2, 2, 128, [1, 64, 65]), (6, 2, 64, [127, 129, 16]), (4, 1, 128, [257, 300]),
@@ -97,13 +110,29 @@ def test_h2o_scores(kind, Hq, Hkv, d, L):
     ev.score(q.cuda(), k.cuda(), L)
     got = ev.scores.cpu().double()
     for b, n in enumerate(L):
-        ref = torch.zeros((Hkv, n), dtype=torch.float64)
-        for h in range(Hq):
-            s = q[b, h, :n].double() @ k[b, h // (Hq // Hkv), :n].double().T / math.sqrt(d)
-            s.masked_fill_(torch.ones(n, n, dtype=torch.bool).triu(1), -math.inf)
-            ref[h // (Hq // Hkv)] += torch.softmax(s, dim=-1).sum(dim=0)
+        ref = _h2o_ref(q[b], k[b], n)
         # terms under 2^-126 are fp32 subnormals, each within 2^-150: a sum of
         # up to 4 * 1030 * 8 of them is REL-exact from 1e-35 on
         err = (got[b, :, :n] - ref).abs() / ref.clamp_min(1e-35)
         assert float(err.max()) <= REL, (b, float(err.max()))
         assert bool((got[b, :, n:] == -1.0).all())
+
+
+@pytest.mark.parametrize("shift", [0.0, -1000.0])
+@pytest.mark.parametrize("masked", [[70], range(64, 128), range(0, 64), range(0, 200), [5, 66, 250]])
+@pytest.mark.parametrize("Hq,Hkv,d,L", [(4, 2, 128, 300), (28, 4, 64, 264)])
+def test_h2o_masked(Hq, Hkv, d, L, masked, shift):
+    """Keys at -inf have no weight, whatever part of a row or a tile they are,
+    and the other keys' logits may lie far below 0."""
+    g = torch.Generator().manual_seed(Hq + d + len(masked))
+    q, k = (torch.randn((1, h, L, d), generator=g).bfloat16() for h in (Hq, Hkv))
+    q[..., 5], q[..., 6] = 1.0, 32.0
+    k[..., 6] = shift * math.sqrt(d) / 32.0
+    k[:, :, list(masked), 5] = -math.inf
+    ev = Evictor(1, L, Hq, Hkv, d, 1, 1, scorer="h2o")
+    ev.scores.fill_(-1.0)
+    ev.score(q.cuda(), k.cuda(), [L])
+    got, ref = ev.scores[0].cpu().double(), _h2o_ref(q[0], k[0], L)
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    err = (got - ref).abs() / ref.clamp_min(1e-35)
+    assert float(err[~torch.isnan(ref)].max()) <= REL
