@@ -213,7 +213,11 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   const int t_lo = kb * kKeys / kT, w_lo = key0 < L ? key0 / kT : nt;      // first tiles
 
   __shared__ Tile s_tile[Stager<D, WAVES>::kBuffers];
-  __shared__ double s_lse[Stager<D, WAVES>::kBuffers][kT];
+  // log-sum-exps of a tile's rows: true, and for the digit path at most kLseMax
+  // (a logit there is under 2^18, so the term is 0, and its exponent stays
+  // within int: another key may take a row's log-sum-exp past 2^31)
+  constexpr double kLseMax = 0x1p30;
+  __shared__ double s_lse[Stager<D, WAVES>::kBuffers][2][kT];
   Stager<D, WAVES> rows{qh, L, nt, wave, lane};
   rows.start(t_lo);
   Stationary<D> sx;
@@ -238,14 +242,17 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   for (int tile = t_lo; tile < nt; ++tile) {
     const int buf = Stager<D, WAVES>::kTwo ? (tile - t_lo) & 1 : 0;
     if (!Stager<D, WAVES>::kTwo && tile > t_lo) __syncthreads();
-    if (tid < kT) s_lse[buf][tid] = lse;
+    if (tid < kT) {
+      s_lse[buf][0][tid] = lse;
+      s_lse[buf][1][tid] = lse > kLseMax ? kLseMax : lse;   // NaN stays
+    }
     lse = fetch_lse(tile + 1);
     Tile& st = rows.stage(s_tile, tile, t_lo);              // its barrier covers s_lse too
     if (tile < w_lo) continue;                              // wave-uniform
     const int rbase = tile * kT;
     const bool edge = rbase < key0 + 31;                    // some rows come before the keys
-    const double* so = s_lse[buf];
     if (st.exact_enough(U, V, cf, lane)) {
+      const double* so = s_lse[buf][1];
       auto pass = [&](auto masked) {
         pipelined_products<D>(st, sx, q4, r16, [&](int kt, int c, const i32x4 (&S)[kSums]) {
           const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
@@ -264,6 +271,7 @@ void h2o_cols_i8_kernel(H2oArgs a) {
       if (edge) pass(std::true_type());
       else      pass(std::false_type());
     } else {
+      const double* so = s_lse[buf][0];
 #pragma unroll 1
       for (int kt = 0; kt < 4; ++kt) {
         f64x4 acc[2];

@@ -136,3 +136,20 @@ def test_h2o_masked(Hq, Hkv, d, L, masked, shift):
     assert torch.equal(torch.isnan(got), torch.isnan(ref))
     err = (got - ref).abs() / ref.clamp_min(1e-35)
     assert float(err[~torch.isnan(ref)].max()) <= REL
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("at", [3, 40, 130])
+@pytest.mark.parametrize("Hq,Hkv,d,L", [(4, 2, 128, 300), (28, 4, 64, 264)])
+def test_h2o_huge_key(Hq, Hkv, d, L, at, sign):
+    """One finite key with logits past 2^31 in base 2: it takes all (or none) of
+    the weight of every row that sees it, also from tiles of ordinary keys."""
+    g = torch.Generator().manual_seed(Hq + d + at)
+    q, k = (torch.randn((1, h, L, d), generator=g).bfloat16() for h in (Hq, Hkv))
+    q[..., 7] = 1.0
+    k[:, :, at, 7] = sign * 2.0 ** 36
+    ev = Evictor(1, L, Hq, Hkv, d, 1, 1, scorer="h2o")
+    ev.scores.fill_(-1.0)
+    ev.score(q.cuda(), k.cuda(), [L])
+    got, ref = ev.scores[0].cpu().double(), _h2o_ref(q[0], k[0], L)
+    assert float(((got - ref).abs() / ref.clamp_min(1e-35)).max()) <= REL
