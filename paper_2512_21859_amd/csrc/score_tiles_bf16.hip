@@ -14,7 +14,8 @@
 // by step and no logit waits in registers for the tile's maximum; a tile that
 // the reference does not fit is redone.  Stores e (fp32, float4 of 4
 // consecutive keys, laid out [tile][16-key step][row][16]) and per (tile, row)
-// the reference in logit units and the sum.
+// the reference in logit units (-inf where the row sees no key of the tile, or
+// none over -inf: the tile then counts nowhere) and the sum.
 
 #include <type_traits>
 
@@ -139,7 +140,7 @@ void score_tiles_i8_kernel(ScoreArgs a) {
         for (int c = 0; c < 2; ++c) {
           const int t = static_cast<int>(group_all(static_cast<uint32_t>(top[c]), IMax()));
           const int over = t == kNone ? 0 : t - ref[c];
-          m[c] = static_cast<double>(ref[c]) * 0.69314718055994530942;
+          m[c] = t == kNone ? -INFINITY : static_cast<double>(ref[c]) * 0.69314718055994530942;
           ref[c] += over;                    // the next tile's reference
           bad = bad || over > kRefLow + kRefSpan || over < kRefLow;
         }
@@ -168,7 +169,7 @@ void score_tiles_i8_kernel(ScoreArgs a) {
               const double t = fma(acc[c][i], cd, -rd[c]);
               const bool ok = 16 * kt + i <= lim[c];
               mx[c] = ok ? fmaxf(mx[c], static_cast<float>(t)) : mx[c];
-              e[i] = ok ? exp2_split(t) : 0.f;
+              e[i] = ok ? exp2_clamped(t) : 0.f;
             }
             z[c] += store_e(c, kt, e);
           }
@@ -178,7 +179,7 @@ void score_tiles_i8_kernel(ScoreArgs a) {
         for (int c = 0; c < 2; ++c) {
           mx[c] = fmaxf(mx[c], __shfl_xor(mx[c], 16));
           mx[c] = fmaxf(mx[c], __shfl_xor(mx[c], 32));
-          m[c] = rd[c] * 0.69314718055994530942;
+          m[c] = mx[c] == -INFINITY ? -INFINITY : rd[c] * 0.69314718055994530942;
           const bool off = round == 0 && fabsf(mx[c]) < INFINITY && !(mx[c] <= kRefLow + kRefSpan && mx[c] >= kRefLow);
           if (off) rd[c] += rint(static_cast<double>(mx[c]));
           redo = redo || off;

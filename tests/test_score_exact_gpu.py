@@ -57,14 +57,7 @@ def test_raw_scores(kind, G, w, d, L):
     B, Hkv, Lmax = len(L), 2, max(L) + 5
     q = _values(kind if kind in ("wide", "normal") else "normal", (B, G * Hkv, w, d), g)
     k = _values(kind, (B, Hkv, Lmax, d), g)
-    ref = _raw64(q, k, L, w, 1.0 / math.sqrt(d))
-    ev = Evictor(B, Lmax, G * Hkv, Hkv, d, w, 1)
-    ev.scores.zero_()
-    ev.score(q.cuda(), k.cuda(), L)
-    got = ev.scores.cpu().double()
-    for b, n in enumerate(L):
-        err = (got[b, :, :n - w] - ref[b, :, :n - w]).abs() / ref[b, :, :n - w].clamp_min(1e-37)
-        assert float(err.max()) <= REL, (b, float(err.max()))
+    _check_raw(q, k, L, w)
 
 
 def test_not_finite():
@@ -80,6 +73,44 @@ def test_not_finite():
     assert torch.isnan(s[70])
     s[70] = 0.0
     assert torch.equal(s, torch.zeros_like(s))
+
+
+def _check_raw(q, k, L, w):
+    ref = _raw64(q, k, L, w, 1.0 / math.sqrt(q.shape[-1]))
+    B, Hq, Hkv, d, Lmax = q.shape[0], q.shape[1], k.shape[1], q.shape[3], k.shape[2]
+    ev = Evictor(B, Lmax, Hq, Hkv, d, w, 1)
+    ev.scores.fill_(-1.0)
+    ev.score(q.cuda(), k.cuda(), L)
+    got = ev.scores.cpu().double()
+    for b, n in enumerate(L):
+        err = (got[b, :, :n - w] - ref[b, :, :n - w]).abs() / ref[b, :, :n - w].clamp_min(1e-37)
+        assert float(err.max()) <= REL, (b, float(err.max()))
+
+
+@pytest.mark.parametrize("big", [1.0, 2.0 ** 12])
+@pytest.mark.parametrize("shift", [-1000.0, -100000.0, 1000.0])
+@pytest.mark.parametrize("w,d,L", [(32, 128, [130, 65]), (32, 64, [161]), (64, 128, [700, 66])])
+def test_far_logits(w, d, L, shift, big):
+    """Every logit far from 0, also where rows of the window see no key of the
+    last tile; `big` takes the products to float64."""
+    g = torch.Generator().manual_seed(w + d + len(L))
+    q = torch.randn((len(L), 4, w, d), generator=g).bfloat16()
+    k = torch.randn((len(L), 2, max(L) + 5, d), generator=g).bfloat16()
+    q[..., 6], q[..., 7] = 32.0, 1.0
+    k[..., 6] = shift * math.sqrt(d) / 32.0
+    q[..., 8], k[..., 8], q[..., 9], k[..., 9] = big, big, big, -big     # cancels, and widens both rows
+    _check_raw(q, k, L, w)
+
+
+@pytest.mark.parametrize("masked", [[70], range(64, 128), range(0, 64), range(0, 120), [5, 66, 150]])
+@pytest.mark.parametrize("w,d", [(16, 128), (32, 64)])
+def test_masked_keys(w, d, masked):
+    """Keys at -inf have no weight, also where they fill a tile."""
+    g = torch.Generator().manual_seed(w + d + len(masked))
+    q, k = torch.randn((1, 6, w, d), generator=g).bfloat16(), torch.randn((1, 2, 200, d), generator=g).bfloat16()
+    q[..., 5] = 1.0
+    k[:, :, list(masked), 5] = -math.inf
+    _check_raw(q, k, [200], w)
 
 
 def _h2o_ref(q, k, n):
