@@ -9,16 +9,17 @@
 // and X_i = d0 2^24 + d1 2^16 + d2 2^8 + d3 with balanced digits d0..d3 in
 // [-128, 127].  Products of digit planes are int8 matrix products, exact in
 // int32: with |d0| <= 64, S_s = sum_{i+j=s} d_i . d'_j over up to 128 elements
-// is at most 2^19, 2^21, 2^22, 6 2^20 for s = 0 .. 3.  The 13 plane pairs with i + j <= 4 are computed (the
-// other three multiply d2 d3', d3 d2', d3 d3': nonzero only where both
-// elements are under 2^-6 of their rows' largest and one under 2^-14).
-// What is left out is bounded for the data at hand: `b` (below) collects
-// 2^15 |d3|_1 (the omitted pairs) and 2^30 |X - x 2^(29-E)|_1 (elements below
-// 2^-22 of the largest, truncated), and a tile whose bound passes kMaxErr in
-// the exponent of the softmax (base 2), or that holds an infinity or a NaN,
-// is computed with float64 products instead.  So every logit has the accuracy
-// of the float64 product up to an error below 2^-25, under the fp32 rounding
-// of its own exponential; on normal data the error is about 2^-36.
+// is at most 2^19, 2^21, 2^22, 6 2^20, 3 2^21 for s = 0 .. 4.  The 13 plane
+// pairs with i + j <= 4 are computed (the other three multiply d2 d3', d3 d2',
+// d3 d3': nonzero only where both elements are under 2^-6 of their rows'
+// largest and one under 2^-14).  What is left out is bounded for the data at
+// hand: `b` (below) collects 2^15 |d3|_1 (the omitted pairs) and
+// 2^30 |X - x 2^(29-E)|_1 (elements below 2^-22 of the largest, truncated), and
+// a tile whose bound passes kMaxErr in the exponent of the softmax (base 2), or
+// that holds an infinity or a NaN, is computed with float64 products instead.
+// So a logit is the exact product (without d3 digits and truncation: nearly
+// always) or within 2^-28 of it, a tenth of the rounding error of its own fp32
+// exponential.
 #pragma once
 
 #include "common.h"
@@ -30,8 +31,10 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 constexpr int kDigits = 4;
 constexpr int kSums = 5;                     // digit sums i + j = 0 .. 4
-constexpr float kMaxErr = 0x1p-25f;          // largest tolerated error of a base-2 exponent
-constexpr float kBase = 0x1p24f;             // floor of the lowest sum, in product units
+constexpr float kMaxErr = 0x1p-28f;          // largest tolerated error of a base-2 exponent
+// Counted as an error of 2^11 product units, so that a tile of digits has
+// |t| < 2^28: its |X . X'| <= 2^67 is 2^56 times this share of the bound.
+constexpr float kBase = 0x1p11f;
 
 // Largest |x| of 8 bf16 as a 15-bit pattern (ordered like the magnitude).
 __device__ __forceinline__ uint32_t absmax8(const uint4& v) {
@@ -414,19 +417,14 @@ __device__ __forceinline__ void pipelined_products(const StreamTile<D>& st, cons
   }
 }
 
-// The dot product behind item i of the sums, in units of 2^24 times the rows'
-// units, exact but for the lowest sum (floored): hi 2^16 + mid with
-// hi = S0 2^8 + S1 and mid = S2 2^8 + S3 + S4 / 2^8, both within int32.  They
-// become float64 as the low words, sign bit flipped, of 2^68 + 2^16 (hi + 2^31)
-// and 2^52 + mid + 2^31 (an integer-to-float64 conversion runs at half rate).
+// The dot product behind item i of the sums, in units of 2^16 times the rows'
+// units: hi 2^24 + mid 2^8 + S4 with hi = S0 2^8 + S1 and mid = S2 2^8 + S3,
+// all within int32, and every step in float64 exact.  (A conversion runs at
+// half rate; integers placed in a float64's low word by bit operations cost the
+// same and hold constants in registers: three of them 2-5% of an H2O call.)
 __device__ __forceinline__ double digit_value(const i32x4 (&S)[kSums], int i) {
-  const uint32_t hi = (static_cast<uint32_t>(S[0][i]) << 8) + static_cast<uint32_t>(S[1][i]);
-  const uint32_t mid = (static_cast<uint32_t>(S[2][i]) << 8) + static_cast<uint32_t>(S[3][i]) +
-                       static_cast<uint32_t>(S[4][i] >> 8);
-  const double a = __longlong_as_double(0x4430000000000000ull | (hi ^ 0x80000000u));
-  const double b = __longlong_as_double(0x4330000000000000ull | (mid ^ 0x80000000u));
-  constexpr double kSub = 0x1p68 + 0x1p52 + 0x1p47 + 0x1p31;
-  return (a - kSub) + b;                                    // every step is exact
+  const int hi = (S[0][i] << 8) + S[1][i], mid = (S[2][i] << 8) + S[3][i];
+  return fma(static_cast<double>(hi), 0x1p24, fma(static_cast<double>(mid), 0x1p8, static_cast<double>(S[4][i])));
 }
 
 // float64 products of the same shape and layout, straight from memory, for

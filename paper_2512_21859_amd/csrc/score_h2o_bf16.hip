@@ -81,8 +81,8 @@ void h2o_rows_i8_kernel(H2oArgs a) {
   const float cf = static_cast<float>(cd);
   const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
   const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
-  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p24),
-                        static_cast<double>(sx.unit[1]) * (cd * 0x1p24)};
+  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p16),
+                        static_cast<double>(sx.unit[1]) * (cd * 0x1p16)};
 
   double ref[2] = {0.0, 0.0}, z[2] = {0.0, 0.0};            // this lane's share of the sum
   bool seen[2] = {false, false};                            // the row has had a logit over -inf
@@ -214,7 +214,7 @@ void h2o_cols_i8_kernel(H2oArgs a) {
 
   __shared__ Tile s_tile[Stager<D, WAVES>::kBuffers];
   // log-sum-exps of a tile's rows: true, and for the digit path at most kLseMax
-  // (a logit there is under 2^18, so the term is 0, and its exponent stays
+  // (a logit there is under 2^28, so the term is 0, and its exponent stays
   // within int: another key may take a row's log-sum-exp past 2^31)
   constexpr double kLseMax = 0x1p30;
   __shared__ double s_lse[Stager<D, WAVES>::kBuffers][2][kT];
@@ -229,8 +229,8 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   const float cf = static_cast<float>(cd);
   const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
   const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
-  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p24),
-                        static_cast<double>(sx.unit[1]) * (cd * 0x1p24)};
+  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p16),
+                        static_cast<double>(sx.unit[1]) * (cd * 0x1p16)};
 
   // log-sum-exp of row tid of a tile, fetched a tile ahead; rows past the
   // prompt: so large that their terms vanish

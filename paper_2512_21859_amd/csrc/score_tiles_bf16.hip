@@ -70,8 +70,8 @@ void score_tiles_i8_kernel(ScoreArgs a) {
   sx.load(col, q4);
   const double cd = a.scale * 1.4426950408889634;           // exp(x) = 2^(x log2 e)
   const float cf = static_cast<float>(cd);
-  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p24),
-                        static_cast<double>(sx.unit[1]) * (cd * 0x1p24)};
+  const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p16),
+                        static_cast<double>(sx.unit[1]) * (cd * 0x1p16)};
   // wave-uniform: scalar registers
   const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
   const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
@@ -119,7 +119,7 @@ void score_tiles_i8_kernel(ScoreArgs a) {
           for (int i = 0; i < 4; ++i) {
             const double v = digit_value(S, i);
             // the sum with 1.5 2^52 holds round(t), t = v f, in its low word
-            // (|t| < 2^18 here)
+            // (|t| < 2^28 here)
             const double y = fma(v, f, 0x1.8p52);
             n[i] = static_cast<int>(static_cast<uint32_t>(__double_as_longlong(y)));
             e[i] = ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(fma(v, f, 0x1.8p52 - y))), n[i] - ref[c]);
