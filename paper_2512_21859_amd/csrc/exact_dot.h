@@ -157,10 +157,11 @@ struct FMax {
   }
 };
 
-// x + (x of lane l ^ 16), then l ^ 32: the sum over the four lane groups, the
-// same in each (float64 through two 32-bit swaps).
-__device__ __forceinline__ double group_sum_f64(double x) {
-  auto swap = [](double v, bool by32) {
+// f over the four lane groups of a float64, the same result in each (through two
+// 32-bit swaps): f(x, x of lane l ^ 16), then l ^ 32.
+template <typename F>
+__device__ __forceinline__ double group_f64(double x, F f) {
+  auto swap = [f](double v, bool by32) {
     const uint64_t u = __double_as_longlong(v);
     const uint32_t lo = static_cast<uint32_t>(u), hi = static_cast<uint32_t>(u >> 32);
     uint32_t l0, l1, h0, h1;
@@ -173,10 +174,16 @@ __device__ __forceinline__ double group_sum_f64(double x) {
       const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
       l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
     }
-    return __longlong_as_double((static_cast<uint64_t>(h0) << 32) | l0) +
-           __longlong_as_double((static_cast<uint64_t>(h1) << 32) | l1);
+    return f(__longlong_as_double((static_cast<uint64_t>(h0) << 32) | l0),
+             __longlong_as_double((static_cast<uint64_t>(h1) << 32) | l1));
   };
   return swap(swap(x, false), true);
+}
+__device__ __forceinline__ double group_sum_f64(double x) {
+  return group_f64(x, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ double group_max_f64(double x) {
+  return group_f64(x, [](double a, double b) { return fmax(a, b); });
 }
 
 // 2^t as fp32 for a float64 t: t = n + f with n = round(t) exact and
@@ -186,6 +193,12 @@ __device__ __forceinline__ double group_sum_f64(double x) {
 __device__ __forceinline__ float exp2_split(double t) {
   const double n = rint(t);
   return ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - n)), static_cast<int>(n));
+}
+// the same for |t| < 2^31, with n as the low word of t + 1.5 2^52
+__device__ __forceinline__ float exp2_short(double t) {
+  const double y = t + 0x1.8p52;
+  return ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - (y - 0x1.8p52))),
+                static_cast<int>(static_cast<uint32_t>(__double_as_longlong(y))));
 }
 // the same for any t: 2^-inf = 0, and n stays within int
 __device__ __forceinline__ float exp2_clamped(double t) {
@@ -414,6 +427,28 @@ __device__ __forceinline__ void pipelined_products(const StreamTile<D>& st, cons
       }
     }
     __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The same without overlap, for a few tiles whose longer `use` would not leave
+// registers for it.
+template <int D, typename F>
+__device__ __forceinline__ void stepwise_products(const StreamTile<D>& st, const Stationary<D>& sx,
+                                                  int q4, int r16, F use) {
+  constexpr int KS = Stationary<D>::KS;
+#pragma unroll 1
+  for (int kt = 0; kt < 4; ++kt) {
+    i32x4 A[KS][kDigits], S[kSums];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int k = 0; k < kDigits; ++k) A[ks][k] = st.get(kt, ks, k, q4, r16);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      digit_products<D>(A, sx, c, S);
+      use(kt, c, S);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 

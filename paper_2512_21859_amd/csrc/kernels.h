@@ -59,7 +59,8 @@ struct H2oArgs {
   float* scores;          // [B][Hkv][Lmax]: accumulated attention for j < L[b]
   double* row_M;          // ws: [B][Hq][Lmax] fp32: row max (logit units);
                           //     bf16: row log-sum-exp (base 2)
-  double* row_Z;          // ws: [B][Hq][Lmax] fp32: row normaliser
+  double* row_Z;          // ws: [B][Hq][Lmax] fp32: row normaliser;
+                          //     bf16: reference of the row's sum (base 2)
   double* col_part;       // ws: [B][Hq][Lmax] per-head column mass
   int32_t B, Lmax, Hq, Hkv;
   int32_t n_ranks;        // set by launch_h2o_passes_bf16: row (key) blocks of the longest sequence

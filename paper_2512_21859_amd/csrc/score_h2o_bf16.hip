@@ -5,12 +5,13 @@
 //     registers as digits; the key tiles up to the diagonal stream through LDS.
 //     Every row keeps an integer base-2 reference and its sum of 2^(t - ref);
 //     a tile whose largest logit passes the reference by 2^60 is redone.  The
-//     row's log-sum-exp in base 2, ref + log2(sum), goes to row_M.
+//     log-sum-exp goes to row_M, the reference to row_Z.
 //   cols: block = WAVES waves of 32 consecutive keys; the query tiles from the
-//     diagonal on stream through LDS, with their log-sum-exps.  Streamed rows
-//     are the MFMA rows, so a lane's 16 logits of a tile belong to one key: it
-//     adds 2^(t - lse) to that key's float64 sum and the lanes meet only at
-//     the end.  Per-head column masses; the caller's merge adds the heads.
+//     diagonal on stream through LDS, with these.
+//     Streamed rows are the MFMA rows, so a lane's 16 logits of a tile belong
+//     to one key: it adds 2^(t - lse) to that key's float64 sum and the lanes
+//     meet only at the end.  Per-head column masses; the caller's merge adds
+//     the heads.
 //
 // Both are bound by vector instructions (about 19 per logit, and 100 per 512
 // streamed elements converted); the products run
@@ -28,6 +29,15 @@ namespace {
 
 constexpr int kT = 64;                       // streamed rows per tile
 constexpr int kNone = -(1 << 29);            // n of a masked logit
+// kinds of passes over a tile: every logit counts; up to the diagonal; the first
+// query tile, whose rows see one tile only.  With few keys the rounding of a
+// row's largest term does not average out, so there the reference is the row's
+// largest logit itself and the sum is not rounded on the way; and the column
+// pass adds the very terms that the row pass summed, over their sum.  (Against
+// 2^(t - lse) throughout, error of the scores from float64: 2 tokens 2.55 ->
+// 2.29e-8, 300 tokens 2.543 -> 2.536e-8; 2.27 and 2.539e-8 with float64 products
+// and a reference for each tile.)
+enum { kPlain, kMasked, kFirst };
 // a reference stands while the tile's largest n is at most kHigh above it, and
 // that of the row's first tile with a logit over -inf at least kLow (the row's
 // largest term then keeps its fp32 precision, and everything under 2^-102 of it
@@ -93,12 +103,13 @@ void h2o_rows_i8_kernel(H2oArgs a) {
     const bool edge = kbase + kT - 1 > row0;
     // take the tile's largest n (or logit) per row into the references; false
     // where a row's reference moved and the tile has to be redone
+    const bool one = w_hi == 1;
     auto settle = [&](const double (&top)[2]) {
       bool moved = false;
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        const double to = rint(top[c]), over = to - ref[c];
-        if (fabs(top[c]) < INFINITY && (over > kHigh || (!seen[c] && over < kLow))) {
+        const double to = one ? top[c] : rint(top[c]), over = to - ref[c];
+        if (fabs(top[c]) < INFINITY && (over > kHigh || (!seen[c] && over < kLow) || (one && over != 0.0))) {
           z[c] = ldexp(z[c], static_cast<int>(fmax(-over, -4000.0)));
           ref[c] = to;
           moved = true;
@@ -108,37 +119,56 @@ void h2o_rows_i8_kernel(H2oArgs a) {
       return __builtin_amdgcn_ballot_w64(moved) == 0;
     };
     if (st.exact_enough(U, V, cf, lane)) {
-      auto pass = [&](auto masked) -> bool {
+      auto pass = [&](auto kind) -> bool {
         asm volatile("" ::: "memory");       // no operand is read ahead of the pass
+        constexpr int kKind = decltype(kind)::value;
         int top[2] = {kNone, kNone}, iref[2];
-        double zt[2] = {0.0, 0.0};
-#pragma unroll
-        for (int c = 0; c < 2; ++c) iref[c] = static_cast<int>(fmin(fmax(ref[c], -0x1p30), 0x1p30));
-        pipelined_products<D>(st, sx, q4, r16, [&](int kt, int c, const i32x4 (&S)[kSums]) {
-          const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
-          float e[4];
-          int n[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const double v = digit_value(S, i);
-            const double y = fma(v, f, 0x1.8p52);           // round(t) in the low word
-            n[i] = static_cast<int>(static_cast<uint32_t>(__double_as_longlong(y)));
-            e[i] = ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(fma(v, f, 0x1.8p52 - y))), n[i] - iref[c]);
-            if constexpr (decltype(masked)::value) {
-              const bool ok = kbase + 16 * kt + 4 * q4 + i <= row0 + 16 * c + r16;
-              n[i] = ok ? n[i] : kNone;
-              e[i] = ok ? e[i] : 0.f;
-            }
-          }
-          top[c] = max(max(top[c], max(n[0], n[1])), max(n[2], n[3]));
-          zt[c] += static_cast<double>((e[0] + e[1]) + (e[2] + e[3]));
-          asm volatile("" : "+v"(zt[c]));    // summed here, not sunk behind the check of the references
-        });
-        double tops[2];
+        double tops[2] = {-INFINITY, -INFINITY}, zt[2] = {0.0, 0.0}, cref[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          const int t = static_cast<int>(group_all(static_cast<uint32_t>(top[c]), IMax()));
-          tops[c] = t == kNone ? -INFINITY : static_cast<double>(t);
+          cref[c] = fmin(fmax(ref[c], -0x1p30), 0x1p30);
+          iref[c] = static_cast<int>(cref[c]);
+        }
+        auto use = [&](int kt, int c, const i32x4 (&S)[kSums]) {
+          const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
+          if constexpr (kKind == kFirst) {   // any reference, terms summed as they are
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double t = digit_value(S, i) * f;
+              const bool ok = kbase + 16 * kt + 4 * q4 + i <= row0 + 16 * c + r16;
+              tops[c] = ok ? fmax(tops[c], t) : tops[c];
+              zt[c] += static_cast<double>(ok ? exp2_short(t - cref[c]) : 0.f);
+            }
+          } else {
+            float e[4];
+            int n[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double v = digit_value(S, i);
+              const double y = fma(v, f, 0x1.8p52);         // round(t) in the low word
+              n[i] = static_cast<int>(static_cast<uint32_t>(__double_as_longlong(y)));
+              e[i] = ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(fma(v, f, 0x1.8p52 - y))), n[i] - iref[c]);
+              if constexpr (kKind == kMasked) {
+                const bool ok = kbase + 16 * kt + 4 * q4 + i <= row0 + 16 * c + r16;
+                n[i] = ok ? n[i] : kNone;
+                e[i] = ok ? e[i] : 0.f;
+              }
+            }
+            top[c] = max(max(top[c], max(n[0], n[1])), max(n[2], n[3]));
+            zt[c] += static_cast<double>((e[0] + e[1]) + (e[2] + e[3]));
+          }
+          asm volatile("" : "+v"(zt[c]));    // summed here, not sunk behind the check of the references
+        };
+        if constexpr (kKind == kFirst) stepwise_products<D>(st, sx, q4, r16, use);
+        else                           pipelined_products<D>(st, sx, q4, r16, use);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          if constexpr (kKind == kFirst) {
+            tops[c] = group_max_f64(tops[c]);
+          } else {
+            const int t = static_cast<int>(group_all(static_cast<uint32_t>(top[c]), IMax()));
+            tops[c] = t == kNone ? -INFINITY : static_cast<double>(t);
+          }
         }
         const bool ok = settle(tops);
         if (ok) {
@@ -147,8 +177,12 @@ void h2o_rows_i8_kernel(H2oArgs a) {
         }
         return ok;
       };
-      bool done = !edge && pass(std::false_type());
-      while (!done) done = pass(std::true_type());          // twice at most
+      if (one) {
+        while (!pass(std::integral_constant<int, kFirst>())) {}              // twice at most
+      } else {
+        bool done = !edge && pass(std::integral_constant<int, kPlain>());
+        while (!done) done = pass(std::integral_constant<int, kMasked>());   // twice at most
+      }
     } else {
       for (int round = 0;; ++round) {
         double zt[2] = {0.0, 0.0}, tops[2] = {-INFINITY, -INFINITY};
@@ -171,10 +205,7 @@ void h2o_rows_i8_kernel(H2oArgs a) {
           }
         }
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          tops[c] = fmax(tops[c], __shfl_xor(tops[c], 16));
-          tops[c] = fmax(tops[c], __shfl_xor(tops[c], 32));
-        }
+        for (int c = 0; c < 2; ++c) tops[c] = group_max_f64(tops[c]);
         if (settle(tops) || round > 0) {
 #pragma unroll
           for (int c = 0; c < 2; ++c)         // a tile without a logit over -inf adds nothing
@@ -188,7 +219,11 @@ void h2o_rows_i8_kernel(H2oArgs a) {
   for (int c = 0; c < 2; ++c) {
     const double Z = group_sum_f64(z[c]);
     const int row = row0 + 16 * c + r16;
-    if (q4 == 0 && row < L) a.row_M[(static_cast<size_t>(b) * a.Hq + h) * a.Lmax + row] = ref[c] + log2(Z);
+    if (q4 == 0 && row < L) {
+      const size_t o = (static_cast<size_t>(b) * a.Hq + h) * a.Lmax + row;
+      a.row_M[o] = ref[c] + log2(Z);
+      a.row_Z[o] = ref[c];
+    }
   }
 }
 
@@ -218,6 +253,7 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   // within int: another key may take a row's log-sum-exp past 2^31)
   constexpr double kLseMax = 0x1p30;
   __shared__ double s_lse[Stager<D, WAVES>::kBuffers][2][kT];
+  __shared__ double s_ref[kT], s_inv[kT];                   // of the first tile's rows: reference, 2^(ref - lse)
   Stager<D, WAVES> rows{qh, L, nt, wave, lane};
   rows.start(t_lo);
   Stationary<D> sx;
@@ -236,9 +272,14 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   // prompt: so large that their terms vanish
   auto fetch_lse = [&](int tile) {
     const int row = tile * kT + tid;
-    return tid < kT && row < L ? a.row_M[hrow + row] : 0x1p20;
+    return tid < kT && row < L ? a.row_M[hrow + row] : kLseMax;
   };
   double lse = fetch_lse(t_lo), sum[2] = {0.0, 0.0};
+  if (kb == 0 && tid < kT) {
+    const double ref = tid < L ? fmin(a.row_Z[hrow + tid], kLseMax) : kLseMax;
+    s_ref[tid] = ref;
+    s_inv[tid] = exp2(ref - lse);
+  }
   for (int tile = t_lo; tile < nt; ++tile) {
     const int buf = Stager<D, WAVES>::kTwo ? (tile - t_lo) & 1 : 0;
     if (!Stager<D, WAVES>::kTwo && tile > t_lo) __syncthreads();
@@ -247,31 +288,31 @@ void h2o_cols_i8_kernel(H2oArgs a) {
       s_lse[buf][1][tid] = lse > kLseMax ? kLseMax : lse;   // NaN stays
     }
     lse = fetch_lse(tile + 1);
-    Tile& st = rows.stage(s_tile, tile, t_lo);              // its barrier covers s_lse too
+    Tile& st = rows.stage(s_tile, tile, t_lo);              // its barrier covers the rows' values too
     if (tile < w_lo) continue;                              // wave-uniform
     const int rbase = tile * kT;
     const bool edge = rbase < key0 + 31;                    // some rows come before the keys
     if (st.exact_enough(U, V, cf, lane)) {
-      const double* so = s_lse[buf][1];
-      auto pass = [&](auto masked) {
-        pipelined_products<D>(st, sx, q4, r16, [&](int kt, int c, const i32x4 (&S)[kSums]) {
+      auto pass = [&](auto kind) {
+        constexpr int kKind = decltype(kind)::value;
+        auto use = [&](int kt, int c, const i32x4 (&S)[kSums]) {
           const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const double t = fma(digit_value(S, i), f, -so[16 * kt + 4 * q4 + i]);
-            const double y = t + 0x1.8p52;                  // round(t) in the low word
-            const int n = static_cast<int>(static_cast<uint32_t>(__double_as_longlong(y)));
-            float p = ldexpf(__builtin_amdgcn_exp2f(static_cast<float>(t - (y - 0x1.8p52))), n);
-            if constexpr (decltype(masked)::value)
-              p = rbase + 16 * kt + 4 * q4 + i >= key0 + 16 * c + r16 ? p : 0.f;
-            sum[c] += static_cast<double>(p);
+            const int r = 16 * kt + 4 * q4 + i;
+            const float p = exp2_short(fma(digit_value(S, i), f, kKind == kFirst ? -s_ref[r] : -s_lse[buf][1][r]));
+            double x = kKind == kFirst ? static_cast<double>(p) * s_inv[r] : static_cast<double>(p);
+            if constexpr (kKind != kPlain) x = rbase + r >= key0 + 16 * c + r16 ? x : 0.0;
+            sum[c] += x;
           }
-        });
+        };
+        if constexpr (kKind == kFirst) stepwise_products<D>(st, sx, q4, r16, use);
+        else                           pipelined_products<D>(st, sx, q4, r16, use);
       };
-      if (edge) pass(std::true_type());
-      else      pass(std::false_type());
+      if (tile == 0) pass(std::integral_constant<int, kFirst>());
+      else if (edge) pass(std::integral_constant<int, kMasked>());
+      else           pass(std::integral_constant<int, kPlain>());
     } else {
-      const double* so = s_lse[buf][0];
 #pragma unroll 1
       for (int kt = 0; kt < 4; ++kt) {
         f64x4 acc[2];
@@ -281,9 +322,9 @@ void h2o_cols_i8_kernel(H2oArgs a) {
         for (int c = 0; c < 2; ++c)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int r = rbase + 16 * kt + 4 * q4 + i;
-            if (r < L && r >= key0 + 16 * c + r16)
-              sum[c] += static_cast<double>(exp2_clamped(fma(acc[c][i], cd, -so[16 * kt + 4 * q4 + i])));
+            const int r = 16 * kt + 4 * q4 + i;
+            if (rbase + r < L && rbase + r >= key0 + 16 * c + r16)
+              sum[c] += static_cast<double>(exp2_clamped(fma(acc[c][i], cd, -s_lse[buf][0][r])));
           }
       }
     }

@@ -184,3 +184,24 @@ def test_h2o_huge_key(Hq, Hkv, d, L, at, sign):
     ev.score(q.cuda(), k.cuda(), [L])
     got, ref = ev.scores[0].cpu().double(), _h2o_ref(q[0], k[0], L)
     assert float(((got - ref).abs() / ref.clamp_min(1e-35)).max()) <= REL
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L", [1, 2, 9])
+def test_h2o_few_keys(L, d):
+    """Rows of a few keys, whose rounding does not average out; a row of one key
+    gives exactly 1."""
+    B, H = 16, 64
+    g = torch.Generator().manual_seed(L + d)
+    q, k = (torch.randn((B, H, L, d), generator=g).bfloat16() for _ in range(2))
+    ev = Evictor(B, L, H, H, d, 1, 1, scorer="h2o")
+    ev.score(q.cuda(), k.cuda(), [L] * B)
+    got = ev.scores.cpu().double()
+    ref = torch.stack([_h2o_ref(q[b], k[b], L) for b in range(B)])
+    if L == 1:
+        assert bool((got == 1.0).all())
+    # fp32 rounding of the score: 2^-24 / sqrt(3) at mantissa 1, 2.5e-8 over all;
+    # of the terms beside the row's largest, which is exact: 2.5e-8 of at most
+    # half the weight.  Together 2.8e-8, and 3.0e-8 allows for 1024 samples; with
+    # the largest term rounded as well it is 3.5e-8 and more
+    assert float(((got - ref) / ref).pow(2).mean().sqrt()) <= 3.0e-8
