@@ -18,8 +18,9 @@
 // a tile whose bound passes kMaxErr in the exponent of the softmax (base 2), or
 // that holds an infinity or a NaN, is computed with float64 products instead.
 // So a logit is the exact product (without d3 digits and truncation: nearly
-// always) or within 2^-28 of it, a tenth of the rounding error of its own fp32
-// exponential.
+// always) or within 2^-26 of it, the rounding to fp32 of its own exponential's
+// argument.  (At 2^-28 the 0.6% of a normal prompt's tiles that hold an element
+// under 2^-22 of its row's largest took float64 products, six times the work.)
 #pragma once
 
 #include "common.h"
@@ -31,10 +32,12 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 constexpr int kDigits = 4;
 constexpr int kSums = 5;                     // digit sums i + j = 0 .. 4
-constexpr float kMaxErr = 0x1p-28f;          // largest tolerated error of a base-2 exponent
-// Counted as an error of 2^11 product units, so that a tile of digits has
-// |t| < 2^28: its |X . X'| <= 2^67 is 2^56 times this share of the bound.
-constexpr float kBase = 0x1p11f;
+constexpr float kMaxErr = 0x1p-26f;          // largest tolerated error of a base-2 exponent
+constexpr float kFarErr = 0x1p-24f;          // a bound past this one is the data's, not one tile's
+constexpr int kF64Run = 8;                   // tiles that then take float64 products unseen
+// Counted as an error of 2^13 product units, so that a tile of digits has
+// |t| < 2^28: its |X . X'| <= 2^67 is 2^54 times this share of the bound.
+constexpr float kBase = 0x1p13f;
 
 // Largest |x| of 8 bf16 as a 15-bit pattern (ordered like the magnitude).
 __device__ __forceinline__ uint32_t absmax8(const uint4& v) {
@@ -310,10 +313,10 @@ struct StreamTile {
   // the group holding rows 16 kt + 4 q4 .. +3
   static __device__ __forceinline__ int group_of(int kt, int q4) { return (16 * kt + 4 * q4) / RPG; }
   // wave-uniform: every product of the tile with the rows (U, V) stays within
-  // kMaxErr of the exponent (false for anything that is not a number)
-  __device__ __forceinline__ bool exact_enough(float U, float V, float c, int lane) const {
+  // `most` of the exponent (false for anything that is not a number)
+  __device__ __forceinline__ bool within(float U, float V, float c, float most, int lane) const {
     const float2 g = grp[lane % NG];
-    return __builtin_amdgcn_ballot_w64(!((V * g.x + U * g.y) * c <= kMaxErr)) == 0;
+    return __builtin_amdgcn_ballot_w64(!((V * g.x + U * g.y) * c <= most)) == 0;
   }
 };
 
@@ -321,6 +324,12 @@ struct StreamTile {
 // groups w MP .. w MP + MP - 1.  4 or 8 waves: two LDS buffers (one barrier a
 // tile) and rows fetched a tile ahead, into registers; 1 or 2 waves: one
 // buffer, the other blocks of the CU fill the gaps.
+//
+// The block decides together (U and V over all its rows, so every wave finds the
+// same) whether a tile's digits will do.  Keys with a channel far above the rest
+// fail in every tile; so a tile far past the bound sends the next ones to
+// float64 products too, without staging, looking or barriers: the waves then run
+// on their own.
 template <int D, int WAVES>
 struct Stager {
   using Tile = StreamTile<D>;
@@ -330,6 +339,7 @@ struct Stager {
   static constexpr int kWin = MP < 4 ? MP : 4;                         // groups held in registers
   const uint16_t* src;                       // row 0
   int n_rows, n_tiles, wave, lane;
+  float U, V, c;                             // of the block's stationary rows (share)
   uint4 raw[kWin];
 
   __device__ __forceinline__ bool stages() const { return wave * MP < Tile::NG; }   // wave-uniform
@@ -347,8 +357,35 @@ struct Stager {
       for (int u = 0; u < kWin; ++u) raw[u] = fetch(tile, u);
     }
   }
-  // Stage a tile and wait for it.  Every wave of the block calls this for the
-  // same tiles from `first` on, so they meet the same barriers.
+  // the bound's factors over the block's waves; every wave, once
+  __device__ __forceinline__ void share(float2 (&uv)[WAVES], float u, float v, float scale) {
+    if (lane == 0) uv[wave] = make_float2(u, v);
+    __syncthreads();
+    U = V = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      U = fmaxf(U, uv[w].x);
+      V = __builtin_elementwise_maximum(V, uv[w].y);
+    }
+    U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(U)));   // scalar registers
+    V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(V)));
+    c = scale;
+  }
+  // Stage a tile and look at it: its digits, or nullptr where they will not do.
+  // The tiles from there to `end` are then for float64 products, and every wave
+  // calls resume(end) behind them.  All waves of the block call these for the
+  // same tiles, so they meet the same barriers.
+  __device__ __forceinline__ const Tile* look(Tile* buf, int tile, int first, int last, int& end) {
+    const Tile& st = stage(buf, tile, first);
+    if (st.within(U, V, c, kMaxErr, lane)) return &st;
+    end = st.within(U, V, c, kFarErr, lane) ? tile + 1 : min(tile + kF64Run, last);
+    return nullptr;
+  }
+  __device__ __forceinline__ void resume(int end) {
+    start(end);
+    __syncthreads();                         // every wave has looked at the tile that failed
+  }
+  // Stage a tile and wait for it.
   __device__ __forceinline__ Tile& stage(Tile* buf, int tile, int first) {
     Tile& st = buf[kTwo ? (tile - first) & 1 : 0];
     if (!kTwo && tile > first) __syncthreads();             // the previous tile has been read
@@ -363,8 +400,14 @@ struct Stager {
 #pragma unroll
         for (int u = 0; u < kWin; ++u) flags |= st.put(wave * MP + u0 + u, lane, raw[u]);
       }
-      if (__builtin_amdgcn_ballot_w64(flags != 0u))         // rare: the groups get their bounds
-        for (int u = 0; u < MP; ++u) st.put_bound(wave * MP + u, lane, fetch(tile, u));
+      if (__builtin_amdgcn_ballot_w64(flags != 0u)) {       // rare: the groups get their bounds
+        if constexpr (MP == kWin) {
+#pragma unroll
+          for (int u = 0; u < MP; ++u) st.put_bound(wave * MP + u, lane, raw[u]);
+        } else {
+          for (int u = 0; u < MP; ++u) st.put_bound(wave * MP + u, lane, fetch(tile, u));
+        }
+      }
       if (kTwo) start(tile + 1);
     }
     __syncthreads();
@@ -462,29 +505,73 @@ __device__ __forceinline__ double digit_value(const i32x4 (&S)[kSums], int i) {
   return fma(static_cast<double>(hi), 0x1p24, fma(static_cast<double>(mid), 0x1p8, static_cast<double>(S[4][i])));
 }
 
-// float64 products of the same shape and layout, straight from memory, for
-// tiles that the digits cannot hold: row and col are the lane's operand rows.
-// The float64 16x16x4 product returns row l/16 + 4 v in item v, so the
-// streamed row behind MFMA row p is 16 kt + 4 (p % 4) + p / 4.  d runs in
-// 32-wide chunks, of which a lane reads 8 consecutive elements (d = 32 c + 8
-// q4 + step); both operands use the same order.
+// float64 products of whole tiles with the wave's rows, straight from memory, for
+// tiles that the digits cannot hold: `src` has the streamed rows (those past the
+// end: the last one), `col` are the lane's two stationary rows.  The float64
+// 16x16x4 product returns row l/16 + 4 v in item v, so the streamed row behind
+// MFMA row p is 16 kt + 4 (p % 4) + p / 4, and item i of t[c][kt] is streamed
+// row 16 kt + 4 q4 + i with the row of column tile c, as in the digit sums.  d
+// runs in 16-wide chunks, of which a lane reads 4 consecutive elements (d =
+// 16 ch + 4 q4 + step) of either operand, a chunk ahead, across tiles too: the
+// first chunk of the next tile comes from HBM, and a wait for it issued behind
+// the caller's stores would wait for those.  The whole tile's logits stay in
+// registers (64), so nothing is computed twice.
 template <int D>
-__device__ __forceinline__ void f64_products(const uint16_t* row, const uint16_t* const (&col)[2], int q4,
-                                             f64x4 (&acc)[2]) {
-  acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-  for (int c = 0; c < D / 32; ++c) {
-    float av[8], b0[8], b1[8];
-    Elem<bf16_t>::widen(ldg16(row + 32 * c + 8 * q4), av);
-    Elem<bf16_t>::widen(ldg16(col[0] + 32 * c + 8 * q4), b0);
-    Elem<bf16_t>::widen(ldg16(col[1] + 32 * c + 8 * q4), b1);
+struct F64Tiles {
+  const uint16_t* src;
+  int n_rows;
+  const uint16_t* col[2];                    // + 4 q4
+  int q4, sub;                               // sub: the lane's streamed row within 16
+  double scale;
+  uint2 next[6];
+
+  __device__ __forceinline__ void fetch(int tile, int ch) {
+    const int base = min(tile * 64, n_rows - 1);
+    const uint16_t* rows = src + static_cast<size_t>(base) * D;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const double x = av[s];
-      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, static_cast<double>(b0[s]), acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, static_cast<double>(b1[s]), acc[1], 0, 0, 0);
+    for (int kt = 0; kt < 4; ++kt)
+      next[kt] = *reinterpret_cast<const uint2*>(rows + min(16 * kt + sub, n_rows - 1 - base) * D + 4 * q4 + 16 * ch);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) next[4 + c] = *reinterpret_cast<const uint2*>(col[c] + 16 * ch);
+  }
+  __device__ __forceinline__ F64Tiles(const uint16_t* s, int n, const uint16_t* const (&rows)[2], int q4_, int r16,
+                                      double scale_, int tile)
+      : src(s), n_rows(n), col{rows[0] + 4 * q4_, rows[1] + 4 * q4_}, q4(q4_), sub(4 * (r16 & 3) + (r16 >> 2)),
+        scale(scale_) {
+    fetch(tile, 0);
+  }
+  // the tile's logits in base-2 units; tiles come in order
+  __device__ __forceinline__ void products(int tile, f64x4 (&t)[2][4]) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) t[0][kt] = t[1][kt] = f64x4{0.0, 0.0, 0.0, 0.0};
+    auto widen = [](const uint2& v, int s) { // element s of 4
+      const uint32_t w = s < 2 ? v.x : v.y;
+      return static_cast<double>(__uint_as_float(s & 1 ? w & 0xffff0000u : w << 16));
+    };
+#pragma unroll 1
+    for (int ch = 0; ch < D / 16; ++ch) {
+      uint2 v[6];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) v[k] = next[k];
+      const bool end = ch == D / 16 - 1;
+      fetch(end ? tile + 1 : tile, end ? 0 : ch + 1);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const double b0 = widen(v[4], s), b1 = widen(v[5], s);
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+          const double x = widen(v[kt], s);
+          t[0][kt] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b0, t[0][kt], 0, 0, 0);
+          t[1][kt] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b1, t[1][kt], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      t[0][kt] *= scale;
+      t[1][kt] *= scale;
     }
   }
-}
+};
 
 }  // namespace tb

@@ -88,17 +88,19 @@ void h2o_rows_i8_kernel(H2oArgs a) {
   for (int c = 0; c < 2; ++c) col[c] = qh + static_cast<size_t>(min(row0 + 16 * c + r16, L - 1)) * D;
   sx.load(col, q4);
   const double cd = a.scale * 1.4426950408889634;
-  const float cf = static_cast<float>(cd);
-  const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
-  const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
+  __shared__ float2 s_uv[WAVES];
+  keys.share(s_uv, sx.U, sx.V, static_cast<float>(cd));
   const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p16),
                         static_cast<double>(sx.unit[1]) * (cd * 0x1p16)};
 
   double ref[2] = {0.0, 0.0}, z[2] = {0.0, 0.0};            // this lane's share of the sum
   bool seen[2] = {false, false};                            // the row has had a logit over -inf
-  for (int tile = 0; tile < t_hi; ++tile) {
-    Tile& st = keys.stage(s_tile, tile, 0);
-    if (tile >= w_hi) continue;                             // wave-uniform
+  for (int tile = 0, end; tile < t_hi;) {
+    const Tile* st = keys.look(s_tile, tile, 0, t_hi, end);
+    if (st && tile >= w_hi) {                               // wave-uniform
+      ++tile;
+      continue;
+    }
     const int kbase = tile * kT;
     const bool edge = kbase + kT - 1 > row0;
     // take the tile's largest n (or logit) per row into the references; false
@@ -118,7 +120,7 @@ void h2o_rows_i8_kernel(H2oArgs a) {
       }
       return __builtin_amdgcn_ballot_w64(moved) == 0;
     };
-    if (st.exact_enough(U, V, cf, lane)) {
+    if (st) {
       auto pass = [&](auto kind) -> bool {
         asm volatile("" ::: "memory");       // no operand is read ahead of the pass
         constexpr int kKind = decltype(kind)::value;
@@ -130,7 +132,7 @@ void h2o_rows_i8_kernel(H2oArgs a) {
           iref[c] = static_cast<int>(cref[c]);
         }
         auto use = [&](int kt, int c, const i32x4 (&S)[kSums]) {
-          const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
+          const double f = st->grp[Tile::group_of(kt, q4)].x * cu[c];
           if constexpr (kKind == kFirst) {   // any reference, terms summed as they are
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -159,8 +161,8 @@ void h2o_rows_i8_kernel(H2oArgs a) {
           }
           asm volatile("" : "+v"(zt[c]));    // summed here, not sunk behind the check of the references
         };
-        if constexpr (kKind == kFirst) stepwise_products<D>(st, sx, q4, r16, use);
-        else                           pipelined_products<D>(st, sx, q4, r16, use);
+        if constexpr (kKind == kFirst) stepwise_products<D>(*st, sx, q4, r16, use);
+        else                           pipelined_products<D>(*st, sx, q4, r16, use);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           if constexpr (kKind == kFirst) {
@@ -183,37 +185,40 @@ void h2o_rows_i8_kernel(H2oArgs a) {
         bool done = !edge && pass(std::integral_constant<int, kPlain>());
         while (!done) done = pass(std::integral_constant<int, kMasked>());   // twice at most
       }
-    } else {
-      for (int round = 0;; ++round) {
-        double zt[2] = {0.0, 0.0}, tops[2] = {-INFINITY, -INFINITY};
-#pragma unroll 1
-        for (int kt = 0; kt < 4; ++kt) {
-          f64x4 acc[2];
-          const int key = min(kbase + 16 * kt + 4 * (r16 & 3) + (r16 >> 2), L - 1);
-          f64_products<D>(kg + static_cast<size_t>(key) * D, col, q4, acc);
+      ++tile;
+      continue;
+    }
+    if (tile < w_hi) {
+      F64Tiles<D> f64(kg, L, col, q4, r16, cd, tile);
+      for (int u = tile; u < min(end, w_hi); ++u) {
+        f64x4 t[2][4];
+        f64.products(u, t);
+        const int first = u * kT + 4 * q4 - (row0 + r16);   // the lane's first key from its rows' diagonal
+        double tops[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            float zs = 0.f;
+        for (int c = 0; c < 2; ++c) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const double t = acc[c][i] * cd;
-              const bool ok = kbase + 16 * kt + 4 * q4 + i <= row0 + 16 * c + r16;
-              tops[c] = ok ? fmax(tops[c], t) : tops[c];
-              zs += ok ? exp2_clamped(fma(acc[c][i], cd, -ref[c])) : 0.f;
-            }
-            zt[c] += static_cast<double>(zs);
-          }
+          for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              tops[c] = first + 16 * kt + i <= 16 * c ? fmax(tops[c], t[c][kt][i]) : tops[c];
+          tops[c] = group_max_f64(tops[c]);
         }
+        settle(tops);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) tops[c] = group_max_f64(tops[c]);
-        if (settle(tops) || round > 0) {
+        for (int c = 0; c < 2; ++c) {
+          double zt = 0.0;
 #pragma unroll
-          for (int c = 0; c < 2; ++c)         // a tile without a logit over -inf adds nothing
-            if (tops[c] > -INFINITY) z[c] += zt[c];
-          break;
+          for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              zt += static_cast<double>(first + 16 * kt + i <= 16 * c ? exp2_clamped(t[c][kt][i] - ref[c]) : 0.f);
+          if (tops[c] > -INFINITY) z[c] += zt;   // a tile without a logit over -inf adds nothing
         }
       }
     }
+    tile = end;
+    keys.resume(end);
   }
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -248,11 +253,12 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   const int t_lo = kb * kKeys / kT, w_lo = key0 < L ? key0 / kT : nt;      // first tiles
 
   __shared__ Tile s_tile[Stager<D, WAVES>::kBuffers];
-  // log-sum-exps of a tile's rows: true, and for the digit path at most kLseMax
-  // (a logit there is under 2^28, so the term is 0, and its exponent stays
-  // within int: another key may take a row's log-sum-exp past 2^31)
+  // log-sum-exps of a tile's rows, for the digit path, at most kLseMax (a logit
+  // there is under 2^28, so the term is 0, and its exponent stays within int:
+  // another key may take a row's log-sum-exp past 2^31)
   constexpr double kLseMax = 0x1p30;
-  __shared__ double s_lse[Stager<D, WAVES>::kBuffers][2][kT];
+  static_assert(Stager<D, WAVES>::kTwo, "a tile's values are written while the one before is read");
+  __shared__ double s_lse[2][kT];
   __shared__ double s_ref[kT], s_inv[kT];                   // of the first tile's rows: reference, 2^(ref - lse)
   Stager<D, WAVES> rows{qh, L, nt, wave, lane};
   rows.start(t_lo);
@@ -262,9 +268,8 @@ void h2o_cols_i8_kernel(H2oArgs a) {
   for (int c = 0; c < 2; ++c) col[c] = kg + static_cast<size_t>(min(key0 + 16 * c + r16, L - 1)) * D;
   sx.load(col, q4);
   const double cd = a.scale * 1.4426950408889634;
-  const float cf = static_cast<float>(cd);
-  const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
-  const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
+  __shared__ float2 s_uv[WAVES];
+  rows.share(s_uv, sx.U, sx.V, static_cast<float>(cd));
   const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p16),
                         static_cast<double>(sx.unit[1]) * (cd * 0x1p16)};
 
@@ -280,54 +285,61 @@ void h2o_cols_i8_kernel(H2oArgs a) {
     s_ref[tid] = ref;
     s_inv[tid] = exp2(ref - lse);
   }
-  for (int tile = t_lo; tile < nt; ++tile) {
-    const int buf = Stager<D, WAVES>::kTwo ? (tile - t_lo) & 1 : 0;
-    if (!Stager<D, WAVES>::kTwo && tile > t_lo) __syncthreads();
-    if (tid < kT) {
-      s_lse[buf][0][tid] = lse;
-      s_lse[buf][1][tid] = lse > kLseMax ? kLseMax : lse;   // NaN stays
-    }
+  for (int tile = t_lo, end; tile < nt;) {
+    const int buf = (tile - t_lo) & 1;
+    if (tid < kT) s_lse[buf][tid] = lse > kLseMax ? kLseMax : lse;           // NaN stays
     lse = fetch_lse(tile + 1);
-    Tile& st = rows.stage(s_tile, tile, t_lo);              // its barrier covers the rows' values too
-    if (tile < w_lo) continue;                              // wave-uniform
+    const Tile* st = rows.look(s_tile, tile, t_lo, nt, end);                 // its barrier covers the rows' values too
     const int rbase = tile * kT;
     const bool edge = rbase < key0 + 31;                    // some rows come before the keys
-    if (st.exact_enough(U, V, cf, lane)) {
+    if (st && tile < w_lo) {                                // wave-uniform
+      ++tile;
+      continue;
+    }
+    if (st) {
       auto pass = [&](auto kind) {
         constexpr int kKind = decltype(kind)::value;
         auto use = [&](int kt, int c, const i32x4 (&S)[kSums]) {
-          const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
+          const double f = st->grp[Tile::group_of(kt, q4)].x * cu[c];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int r = 16 * kt + 4 * q4 + i;
-            const float p = exp2_short(fma(digit_value(S, i), f, kKind == kFirst ? -s_ref[r] : -s_lse[buf][1][r]));
+            const float p = exp2_short(fma(digit_value(S, i), f, kKind == kFirst ? -s_ref[r] : -s_lse[buf][r]));
             double x = kKind == kFirst ? static_cast<double>(p) * s_inv[r] : static_cast<double>(p);
             if constexpr (kKind != kPlain) x = rbase + r >= key0 + 16 * c + r16 ? x : 0.0;
             sum[c] += x;
           }
         };
-        if constexpr (kKind == kFirst) stepwise_products<D>(st, sx, q4, r16, use);
-        else                           pipelined_products<D>(st, sx, q4, r16, use);
+        if constexpr (kKind == kFirst) stepwise_products<D>(*st, sx, q4, r16, use);
+        else                           pipelined_products<D>(*st, sx, q4, r16, use);
       };
       if (tile == 0) pass(std::integral_constant<int, kFirst>());
       else if (edge) pass(std::integral_constant<int, kMasked>());
       else           pass(std::integral_constant<int, kPlain>());
-    } else {
-#pragma unroll 1
-      for (int kt = 0; kt < 4; ++kt) {
-        f64x4 acc[2];
-        const int row = min(rbase + 16 * kt + 4 * (r16 & 3) + (r16 >> 2), L - 1);
-        f64_products<D>(qh + static_cast<size_t>(row) * D, col, q4, acc);
+      ++tile;
+      continue;
+    }
+    const int lo = max(tile, w_lo);
+    if (lo < end) {
+      F64Tiles<D> f64(qh, L, col, q4, r16, cd, lo);
+      for (int u = lo; u < end; ++u) {
+        f64x4 t[2][4];
+        f64.products(u, t);
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int r = 16 * kt + 4 * q4 + i;
-            if (rbase + r < L && rbase + r >= key0 + 16 * c + r16)
-              sum[c] += static_cast<double>(exp2_clamped(fma(acc[c][i], cd, -s_lse[buf][0][r])));
+            const int r = u * kT + 16 * kt + 4 * q4 + i;
+            const double o = a.row_M[hrow + min(r, L - 1)];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+              if (r < L && r >= key0 + 16 * c + r16) sum[c] += static_cast<double>(exp2_clamped(t[c][kt][i] - o));
           }
       }
     }
+    tile = end;
+    lse = fetch_lse(end);
+    rows.resume(end);
   }
 #pragma unroll
   for (int c = 0; c < 2; ++c) {

@@ -69,50 +69,70 @@ void score_tiles_i8_kernel(ScoreArgs a) {
   }
   sx.load(col, q4);
   const double cd = a.scale * 1.4426950408889634;           // exp(x) = 2^(x log2 e)
-  const float cf = static_cast<float>(cd);
   const double cu[2] = {static_cast<double>(sx.unit[0]) * (cd * 0x1p16),
                         static_cast<double>(sx.unit[1]) * (cd * 0x1p16)};
-  // wave-uniform: scalar registers
-  const float U = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.U)));
-  const float V = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sx.V)));
+  __shared__ float2 s_uv[WAVES];
+  keys.share(s_uv, sx.U, sx.V, static_cast<float>(cd));
 
   if (!active) {                             // waves without rows only stage
-    for (int tile = t_lo; tile < t_hi; ++tile) keys.stage(s_tile, tile, t_lo);
+    for (int tile = t_lo, end; tile < t_hi;) {
+      if (keys.look(s_tile, tile, t_lo, t_hi, end)) {
+        ++tile;
+      } else {
+        tile = end;
+        keys.resume(end);
+      }
+    }
     return;
   }
 
-  int ref[2] = {0, 0};                       // of this lane's rows, base-2 units
-  for (int tile = t_lo; tile < t_hi; ++tile) {
-    Tile& st = keys.stage(s_tile, tile, t_lo);
+  // Every lane stores, the same count on every path: the four lane groups hold
+  // the same sum, and padding rows are copies of row R - 1.  So a wait for the
+  // keys fetched before the stores need not wait for the stores.
+  auto store_e = [&](int tile, int c, int kt, const float (&e)[4]) {
+    const f32x4n x = {e[0], e[1], e[2], e[3]};
+    const size_t te = (bg * a.n_tiles + tile) * R;
+    uint32_t off = (row[c] * 16 + 4 * q4) * 4;
+    asm volatile("" : "+v"(off));            // added here, not once per step ahead of the loop
+    f32x4n* p = reinterpret_cast<f32x4n*>(
+        reinterpret_cast<char*>(a.e + (te * 4 + static_cast<size_t>(kt) * R) * 16) + off);
+    if constexpr (STREAM) __builtin_nontemporal_store(x, p);
+    else                  *p = x;
+    return static_cast<double>((e[0] + e[1]) + (e[2] + e[3]));
+  };
+  auto store_stats = [&](int tile, const double (&m)[2], const double (&z)[2]) {
+    const size_t te = (bg * a.n_tiles + tile) * R;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      uint32_t mo = row[c] * 8;
+      asm volatile("" : "+v"(mo));
+      *reinterpret_cast<double*>(reinterpret_cast<char*>(a.tile_m + te) + mo) = m[c];
+      *reinterpret_cast<double*>(reinterpret_cast<char*>(a.tile_z + te) + mo) = group_sum_f64(z[c]);
+    }
+  };
+  // last key of a tile that the lane's rows see, from the lane's first key on
+  auto limits = [&](int tile, int (&lim)[2]) {
     const int kbase = tile * kT;
     const bool edge = kbase + kT > L - w;                   // some rows do not see all 64 keys
-    int lim[2] = {63, 63};                                  // last key the rows see
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-      if (edge) lim[c] = min(L - 1, L - w + row[c] % w) - kbase - 4 * q4;
-    // Every lane stores, the same count on every path: the four lane groups
-    // hold the same sum, and padding rows are copies of row R - 1.  So a wait
-    // for the keys fetched before the stores need not wait for the stores.
-    const size_t te = (bg * a.n_tiles + tile) * R;
-    auto store_e = [&](int c, int kt, const float (&e)[4]) {
-      const f32x4n x = {e[0], e[1], e[2], e[3]};
-      uint32_t off = (row[c] * 16 + 4 * q4) * 4;
-      asm volatile("" : "+v"(off));          // added here, not once per step ahead of the loop
-      f32x4n* p = reinterpret_cast<f32x4n*>(
-          reinterpret_cast<char*>(a.e + (te * 4 + static_cast<size_t>(kt) * R) * 16) + off);
-      if constexpr (STREAM) __builtin_nontemporal_store(x, p);
-      else                  *p = x;
-      return static_cast<double>((e[0] + e[1]) + (e[2] + e[3]));
-    };
-    double m[2], z[2] = {0.0, 0.0};
-    if (st.exact_enough(U, V, cf, lane)) {
+    for (int c = 0; c < 2; ++c) lim[c] = edge ? min(L - 1, L - w + row[c] % w) - kbase - 4 * q4 : 63;
+    return edge;
+  };
+
+  int ref[2] = {0, 0};                       // of this lane's rows, base-2 units
+  for (int tile = t_lo, end; tile < t_hi;) {
+    const Tile* st = keys.look(s_tile, tile, t_lo, t_hi, end);
+    int lim[2];
+    if (st) {
+      const bool edge = limits(tile, lim);
+      double m[2], z[2] = {0.0, 0.0};
       // false: a reference did not fit, and has been set
       auto pass = [&](auto masked) -> bool {
         asm volatile("" ::: "memory");       // no operand is read ahead of the pass
         int top[2] = {kNone, kNone};
         z[0] = z[1] = 0.0;
-        pipelined_products<D>(st, sx, q4, r16, [&](int kt, int c, const i32x4 (&S)[kSums]) {
-          const double f = st.grp[Tile::group_of(kt, q4)].x * cu[c];
+        pipelined_products<D>(*st, sx, q4, r16, [&](int kt, int c, const i32x4 (&S)[kSums]) {
+          const double f = st->grp[Tile::group_of(kt, q4)].x * cu[c];
           float e[4];
           int n[4];
 #pragma unroll
@@ -133,7 +153,7 @@ void score_tiles_i8_kernel(ScoreArgs a) {
             }
           }
           top[c] = max(max(top[c], max(n[0], n[1])), max(n[2], n[3]));
-          z[c] += store_e(c, kt, e);
+          z[c] += store_e(tile, c, kt, e);
         });
         bool bad = false;
 #pragma unroll
@@ -150,50 +170,38 @@ void score_tiles_i8_kernel(ScoreArgs a) {
       // that does not fit
       bool done = !edge && pass(std::false_type());
       while (!done) done = pass(std::true_type());
-    } else {
-      // the same with float64 products; only the reference may be any float64
-      double rd[2] = {static_cast<double>(ref[0]), static_cast<double>(ref[1])};
-      for (int round = 0;; ++round) {
-        float mx[2] = {-INFINITY, -INFINITY};
-        z[0] = z[1] = 0.0;
-#pragma unroll 1
+      store_stats(tile, m, z);
+      ++tile;
+      continue;
+    }
+    // float64 products; the reference is the tile's own largest logit
+    F64Tiles<D> f64(kg, L, col, q4, r16, cd, tile);
+    for (; tile < end; ++tile) {
+      limits(tile, lim);
+      f64x4 t[2][4];
+      f64.products(tile, t);
+      double m[2], z[2] = {0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        double top = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) top = 16 * kt + i <= lim[c] ? fmax(top, t[c][kt][i]) : top;
+        top = group_max_f64(top);
+        m[c] = top * 0.69314718055994530942;
+        const double r = top == -INFINITY ? 0.0 : top;
+#pragma unroll
         for (int kt = 0; kt < 4; ++kt) {
-          f64x4 acc[2];
-          const int key = min(kbase + 16 * kt + 4 * (r16 & 3) + (r16 >> 2), L - 1);
-          f64_products<D>(kg + static_cast<size_t>(key) * D, col, q4, acc);
+          float e[4];
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            float e[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const double t = fma(acc[c][i], cd, -rd[c]);
-              const bool ok = 16 * kt + i <= lim[c];
-              mx[c] = ok ? fmaxf(mx[c], static_cast<float>(t)) : mx[c];
-              e[i] = ok ? exp2_clamped(t) : 0.f;
-            }
-            z[c] += store_e(c, kt, e);
-          }
+          for (int i = 0; i < 4; ++i) e[i] = 16 * kt + i <= lim[c] ? exp2_clamped(t[c][kt][i] - r) : 0.f;
+          z[c] += store_e(tile, c, kt, e);
         }
-        bool redo = false;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          mx[c] = fmaxf(mx[c], __shfl_xor(mx[c], 16));
-          mx[c] = fmaxf(mx[c], __shfl_xor(mx[c], 32));
-          m[c] = mx[c] == -INFINITY ? -INFINITY : rd[c] * 0.69314718055994530942;
-          const bool off = round == 0 && fabsf(mx[c]) < INFINITY && !(mx[c] <= kRefLow + kRefSpan && mx[c] >= kRefLow);
-          if (off) rd[c] += rint(static_cast<double>(mx[c]));
-          redo = redo || off;
-        }
-        if (__builtin_amdgcn_ballot_w64(redo) == 0) break;
       }
+      store_stats(tile, m, z);
     }
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      uint32_t mo = row[c] * 8;
-      asm volatile("" : "+v"(mo));
-      *reinterpret_cast<double*>(reinterpret_cast<char*>(a.tile_m + te) + mo) = m[c];
-      *reinterpret_cast<double*>(reinterpret_cast<char*>(a.tile_z + te) + mo) = group_sum_f64(z[c]);
-    }
+    keys.resume(end);
   }
 }
 

@@ -113,6 +113,20 @@ def test_masked_keys(w, d, masked):
     _check_raw(q, k, [200], w)
 
 
+@pytest.mark.parametrize("Hq,Hkv,w,d,L", [(64, 8, 32, 128, 8250), (64, 8, 32, 64, 8250), (64, 32, 16, 128, 8200),
+                                          (64, 32, 32, 64, 8200), (64, 16, 32, 128, 8200)])
+def test_float64_runs(Hq, Hkv, w, d, L):
+    """Blocks of several tiles whose keys leave the digits' range for a while, for
+    one tile or a few, at the start and at the end of a prompt."""
+    g = torch.Generator().manual_seed(Hkv + w + d)
+    q, k = torch.randn((1, Hq, w, d), generator=g).bfloat16(), torch.randn((1, Hkv, L, d), generator=g).bfloat16()
+    for lo, hi in ((0, 70), (300, 301), (900, 2100), (2300, 2400), (4000, 4064), (L - 200, L)):
+        k[:, :, lo:hi, 3] *= 300
+    k[:, ::2, 5000:6000, 3] *= 300
+    k[:, 1::2, 6100:6101, 3] = 2.0 ** -40    # truncated: one tile past the bound, but not far
+    _check_raw(q, k, [L], w)
+
+
 def _h2o_ref(q, k, n):
     """Column sums of the causal softmax of one sequence in float64 (NaN where a
     row without a finite logit reaches)."""
