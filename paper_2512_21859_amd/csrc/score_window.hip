@@ -124,7 +124,12 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
   const bool active = row0 + kWaveRows * pair < R && kbase < L;
 
   __shared__ float qs[kRows][kDC + 1];             // +1: conflict-free column reads
-  __shared__ double ks[NS * kT][kDC + 1];        // keys staged as float64: every wave reads them
+  // Keys staged as float64 (every wave reads them).  Two doubles of padding per
+  // 16 rows spread the staging's 8 rows x 4 positions of a half wave over all
+  // banks (the rows are permuted, see krow).  Without it, 4-way conflicts:
+  // L = 65536, 224 rows, 4 KV heads, traced, 323 -> 301 us.
+  __shared__ double s_keys[NS * kT * (kDC + 1) + NS * kT / 8];
+  auto ks = [&](int r) { return &s_keys[r * (kDC + 1) + (r >> 4) * 2]; };
   __shared__ int s_lim[kRows];                     // last key a row sees (-1: padding)
   if (tid < kRows) {
     const int r = row0 + tid;
@@ -168,7 +173,7 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
     for (int e = 0; e < 16; ++e) qs[qrow][qoff + e] = qv[e];
     if (tid < NS * 256) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ks[krow][kdp + e] = static_cast<double>(kv[e]);
+      for (int e = 0; e < 8; ++e) ks(krow)[kdp + e] = static_cast<double>(kv[e]);
     }
   };
 
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
         for (int rt = 0; rt < 2; ++rt)
           av[rt] = static_cast<double>(qs[kWaveRows * pair + 16 * rt + r16][dd]);
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) bv[kt] = ks[(tile - t0) * kT + 16 * kt + r16][dd];
+        for (int kt = 0; kt < 4; ++kt) bv[kt] = ks((tile - t0) * kT + 16 * kt + r16)[dd];
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
