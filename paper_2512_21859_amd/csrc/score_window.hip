@@ -261,19 +261,20 @@ __global__ __launch_bounds__(kTilesThreads, 2) void score_tiles_kernel(ScoreArgs
   }
 }
 
-// Global max and normaliser of 16 rows per block over their tiles: thread
-// (phase, row) merges the row's tiles phase, phase + 64, ..., eight at a time
-// (16 rows' values are one 128-byte line), then the phases are merged.
-constexpr int kStatRows = 16, kStatPhases = 64, kStatThreads = kStatRows * kStatPhases;
-__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(ScoreArgs a) {
+// Global max and normaliser of ROWS rows per block over their tiles: thread
+// (phase, row) merges the row's tiles phase, phase + 64, ..., eight at a time,
+// then the phases are merged.
+constexpr int kStatPhases = 64;
+template <int ROWS>
+__global__ __launch_bounds__(ROWS * kStatPhases) void row_stats_kernel(ScoreArgs a) {
   const int g = blockIdx.y, b = blockIdx.z;
-  const int rr = threadIdx.x % kStatRows, ph = threadIdx.x / kStatRows;
-  const int r = blockIdx.x * kStatRows + rr;
+  const int rr = threadIdx.x % ROWS, ph = threadIdx.x / ROWS;
+  const int r = blockIdx.x * ROWS + rr;
   const int nt = (a.L[b] + kT - 1) / kT;
   const size_t bg = static_cast<size_t>(b) * a.Hkv + g;
   const size_t o = bg * a.n_tiles * a.R + min(r, a.R - 1);
-  constexpr int kWaves = kStatThreads / 64;
-  __shared__ double s_m[kWaves][kStatRows], s_z[kWaves][kStatRows];
+  constexpr int kWaves = ROWS * kStatPhases / 64;
+  __shared__ double s_m[kWaves][ROWS], s_z[kWaves][ROWS];
   constexpr int kAhead = 8;
   double M = -INFINITY, Z = 0.0;
   for (int t0 = ph; t0 < nt; t0 += kStatPhases * kAhead) {
@@ -297,16 +298,16 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(ScoreArgs a) {
     M = top;
   }
   const double own = M;
-  M = fmax(M, __shfl_xor(M, 16));
-  M = fmax(M, __shfl_xor(M, 32));
-  if ((threadIdx.x & 63) < kStatRows) s_m[threadIdx.x >> 6][rr] = M;
+#pragma unroll
+  for (int off = ROWS; off < 64; off <<= 1) M = fmax(M, __shfl_xor(M, off));
+  if ((threadIdx.x & 63) < ROWS) s_m[threadIdx.x >> 6][rr] = M;
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kWaves; ++k) M = fmax(M, s_m[k][rr]);
   Z = own == -INFINITY ? 0.0 : Z * exp(own - M);
-  Z += __shfl_xor(Z, 16);
-  Z += __shfl_xor(Z, 32);
-  if ((threadIdx.x & 63) < kStatRows) s_z[threadIdx.x >> 6][rr] = Z;
+#pragma unroll
+  for (int off = ROWS; off < 64; off <<= 1) Z += __shfl_xor(Z, off);
+  if ((threadIdx.x & 63) < ROWS) s_z[threadIdx.x >> 6][rr] = Z;
   __syncthreads();
   if (ph == 0 && r < a.R) {
     Z = s_z[0][rr];
@@ -455,7 +456,15 @@ hipError_t launch_score(const ScoreArgs& args, int d, bool bf16, hipStream_t st)
   a.stream_e = e_bytes > 256.0 * (1 << 20);
   hipError_t err = bf16 ? launch_score_tiles_bf16(a, d, st) : launch_tiles_f32(a, d, st);
   if (err != hipSuccess) return err;
-  row_stats_kernel<<<dim3((a.R + kStatRows - 1) / kStatRows, a.Hkv, a.B), kStatThreads, 0, st>>>(a);
+  // 8 rows a block keep more CUs busy; past the L2 the half lines they read are
+  // fetched twice, and 16 rows (whole lines) win.  Traced, 8 / 16 rows: L = 8192,
+  // 4 KV heads of 224 rows 3.9 / 4.8 us, 32768 6.5 / 8.4, 65536 8.2 / 11.2,
+  // 131072, 8 heads of 256 rows (67 MB) 24.6 / 21.7.
+  const double stat_bytes = 16.0 * a.R * a.n_tiles * a.Hkv * a.B;
+  if (stat_bytes <= 32.0 * (1 << 20))
+    row_stats_kernel<8><<<dim3((a.R + 7) / 8, a.Hkv, a.B), 8 * kStatPhases, 0, st>>>(a);
+  else
+    row_stats_kernel<16><<<dim3((a.R + 15) / 16, a.Hkv, a.B), 16 * kStatPhases, 0, st>>>(a);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   const dim3 g3((a.Lmax + kT - 1) / kT, a.Hkv, a.B);
