@@ -270,7 +270,7 @@ struct StreamTile {
   static constexpr int LPR = D / 8;          // lanes per row (8 elements each)
   static constexpr int RPG = 64 / LPR;       // rows per group
   static constexpr int NG = 64 / RPG;        // groups per tile (16 or 8)
-  uint8_t dig[kDigits][64 * D];
+  alignas(16) uint8_t dig[kDigits][64 * D];  // read 16 bytes at a time
   float2 grp[NG];
 
   static __device__ __forceinline__ int swz(int r) { return D == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
