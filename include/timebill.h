@@ -109,7 +109,10 @@ size_t tb_workspace_bytes(int32_t op, int32_t B, int32_t Lmax, int32_t Hq,
  *          softmax_j'(q_win[h][i] . k[j'] / sqrt(d)),  j' <= L[b] - w + i,
  *   scores[j] = max of A over |j - j'| <= pool/2 within the prefix.
  * raw_scores (nullable, same layout) receives A before pooling.
- * Arithmetic: float64 dot products, exponentials and sums; fp32 output.
+ * Arithmetic: float64 dot products (bf16: exact ones from integer digit
+ * products; 64-key tiles whose digits could be more than 2^-26 off in the
+ * base-2 exponent are taken in float64) and sums, exponentials with their
+ * argument reduced in float64 and 2^f, |f| <= 1/2, in fp32; fp32 output.
  * L: [host][B].  Requires w >= 1, odd pool >= 1, w < L[b] <= Lmax.
  * ws: tb_workspace_bytes(TB_OP_SCORE, B, Lmax, Hq, Hkv, d, w, 0) bytes. */
 tb_status tb_score_window(const void* q_win, const void* k, int32_t B,
@@ -148,9 +151,9 @@ tb_status tb_score_knorm(const void* k, int32_t B, const int32_t* L, int32_t Lma
  * causal softmax of Sec. 4.2.  tb_select_topk then keeps the largest prefix
  * scores plus the last w positions (the recent window).
  *   q: [B][Hq][Lmax][d], the prefill's queries at every prompt position.
- * Arithmetic: float64 dot products and sums (two passes over the causal
- * product: row statistics, then column mass), fp32 output.  Cost grows as
- * L^2: about 2 Hq L^2 d flops per call.
+ * Arithmetic as tb_score_window (two passes over the causal product: row
+ * statistics, then column mass), fp32 output.  Cost grows as L^2: about
+ * 2 Hq L^2 d operations per call.
  * L: [host][B].  Requires 1 <= L[b] <= Lmax.
  * ws: tb_workspace_bytes(TB_OP_H2O, B, Lmax, Hq, Hkv, d, 0, 0) bytes. */
 tb_status tb_score_h2o(const void* q, const void* k, int32_t B, const int32_t* L,
