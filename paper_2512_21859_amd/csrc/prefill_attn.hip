@@ -488,26 +488,44 @@ hipError_t launch_prefill(const PrefillArgs& a, int d, hipStream_t st) {
   //   query tile's serial steps set the time; twice the blocks with half
   //   the work per step: 49 -> 58 at N = 256, 124 -> 144 at 512, 284 -> 301
   //   at 1024 (at 2048 it lost 7%, at 4096 27%);
-  // * where the heaviest block's chain of steps is the time (64-row blocks few
-  //   enough for about two rounds), two waves share a row tile and halve the
-  //   chain, 8 waves and 128-key stages.  us per call, without / with, 28
-  //   heads of d = 128 (one block per CU): N = 257 8.4 / 7.8, 512 12.9 / 10.8,
-  //   1001 23.9 / 22.2, but 200 7.2 / 7.4, 1300 33.2 / 33.8; 14 heads of
-  //   d = 64 (two per CU): 512 9.2 / 6.9, 1001 15.2 / 10.1, 2048 32.1 / 18.4,
-  //   4096 (896 blocks) 62.9 / 49.2, 8192 149.5 / 154.9; four sequences of
-  //   1001 (896 blocks) 16.9 / 18.8.
+  // * where the heaviest block's chain of steps is the time (few enough 64-row
+  //   blocks), two waves share a row tile and halve the chain, 8 waves and
+  //   128-key stages.  Ratios of the times, split / not, around each line:
+  //   d = 128 (one block per CU): 28 heads N = 200 1.03, 257 0.92, 512 0.84,
+  //   1001 0.93; up to 256 blocks always ahead (48 heads N = 300, 240 blocks,
+  //   0.94), and from there to 512 blocks, a second round, behind at 48 heads
+  //   (N = 321 1.10, 640 1.02) and 64 (257 1.23, 512 1.10) but ahead from
+  //   N = 768 on (28 heads 0.86-0.98, 32 heads 0.86-0.94), where 512 blocks
+  //   are at most 42 heads; 40 heads N = 800, 520 blocks, 1.17.  (28-40 heads
+  //   at 577-767 tokens would gain too, 0.77-0.97; one line for both has not
+  //   been found.)  Past 1024 tokens 28 heads lose (N = 1300 1.02).
+  //   d = 128, batches (whole sequences to an XCD, unevenly loaded): up to 192
+  //   blocks ahead (24 heads, two of 257, 0.93; 8 heads, two of 900, 0.76),
+  //   from 208 on mixed (28 heads, two of 257, 224 blocks, 1.20; 16 heads,
+  //   four of 270, 208 blocks, 1.24, but two of 400, 208 blocks, 0.87).
+  //   d = 64 (two blocks per CU): 14 heads N = 192 0.98, 193 0.93, 512 0.75,
+  //   1024 0.67, 2048 0.60, 4096 (896 blocks) 0.83; 64 heads N = 512 (512
+  //   blocks) 0.83; 28 heads N = 2048 (896) 0.88, 3000 (1316) 1.04; 14 heads,
+  //   two of 3000 (882) 0.96, four of 1500 (1120) 1.13.
+  //   d = 64, batches of up to 1024 tokens go by the blocks of the busiest XCD
+  //   (32 CUs) if all sequences were the longest's length: below 300 tokens
+  //   36 0.95-0.98, 42-48 0.97-1.05, 56-64 1.01-1.08; below 512 56-64
+  //   0.92-0.99, 70-84 1.0-1.14; from 512 on 70-90 0.84-0.90, 96 0.86-1.05,
+  //   105-112 1.00-1.06.
   int lmax = 0;
   long long blocks = 0;                      // of 64 rows
   for (int b = 0; b < a.B; ++b) {
     lmax = max(lmax, a.L[b]);
     blocks += static_cast<long long>((a.L[b] + 63) / 64) * a.Hq;
   }
-  // at d = 128 a second round of blocks only pays behind a long chain, and
-  // batches leave the XCDs unevenly loaded (two sequences of 270, 28 heads:
-  // 9.2 / 10.9 us)
-  const bool chain =
-      d == 128 ? lmax > 256 && lmax <= 1024 && blocks <= (a.B > 1 ? 192 : lmax >= 768 ? 512 : 256)
-               : lmax > 192 && lmax < 8192 && blocks <= (lmax <= 1024 ? 512 : 1024);
+  const long long per_xcd = (static_cast<long long>((lmax + 63) / 64) * a.B * a.Hkv + 7) / 8 * (a.Hq / a.Hkv);
+  bool chain;
+  if (d == 128)
+    chain = lmax > 256 && lmax <= 1024 && blocks <= (a.B > 1 ? 192 : lmax >= 768 ? 512 : 256);
+  else if (lmax > 1024)
+    chain = lmax < 8192 && blocks <= 1024;
+  else
+    chain = lmax > 192 && (a.B == 1 ? blocks <= 512 : per_xcd <= (lmax < 300 ? 36 : lmax < 512 ? 64 : 90));
   if (chain) return launch_prefill_cq<1, 8, 128, 2>(a, d, lmax, st);
   if (lmax <= 1024) return launch_prefill_cq<1, 4, 64, 1>(a, d, lmax, st);
   if (lmax < 8192) return launch_prefill_cq<2, 4, 64, 1>(a, d, lmax, st);
