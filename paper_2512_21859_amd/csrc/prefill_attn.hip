@@ -197,7 +197,7 @@ void prefill_attn_kernel(PrefillArgs a) {
     accL[cq] = f32x4{0.f, 0.f, 0.f, 0.f};
     m_ref[cq] = kFirstRef;
     m_thr[cq] = kFirstRef;
-    m_sc[cq] = kFirstRef * a.scale_log2;
+    m_sc[cq] = SPLIT > 1 ? kFirstRef * a.scale_log2 : -INFINITY;
     l_part[cq] = 0.f;
     m_max[cq] = -INFINITY;
   }

@@ -16,6 +16,8 @@
 // consecutive keys, laid out [tile][16-key step][row][16]) and per (tile, row)
 // the reference in logit units (-inf where the row sees no key of the tile, or
 // none over -inf: the tile then counts nowhere) and the sum.
+// A tile that the digits cannot hold takes float64 products (F64Tiles), its own
+// largest logit as the reference.
 
 #include <type_traits>
 

@@ -12,9 +12,9 @@
 //   K1 score_tiles: the softmax numerators e = exp(s - m) (fp32) of every
 //      (window row, key) with a reference m per (row, 64-key tile), and
 //      z = sum e.  bf16: exact digit products on the int8 matrix cores
-//      (score_tiles_bf16.hip; L = 131072, 8 KV heads, 256 rows: 417 us against
-//      1241 with the float64 products, L = 8192, 4 KV heads, 224 rows: 25
-//      against 46).  fp32 (below): block = (64-key tile, <= 256 window rows) of
+//      (score_tiles_bf16.hip; traced, L = 131072, 8 KV heads, 256 rows: 434 us
+//      against 1288 with float64 products, L = 8192, 4 KV heads, 224 rows: 24
+//      against 47).  fp32 (below): block = (64-key tile, <= 256 window rows) of
 //      one KV head, 512 threads; wave w owns 32 rows x the 64 keys (waves
 //      whose rows are all padding skip the products).  With 4, 6 or 7 row
 //      pairs and enough blocks, a block instead takes 8 consecutive units (32

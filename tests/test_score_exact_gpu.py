@@ -60,19 +60,27 @@ def test_raw_scores(kind, G, w, d, L):
     _check_raw(q, k, L, w)
 
 
-def test_not_finite():
-    """A NaN or infinite key spoils its own column only by the row sums: the
-    other tiles are still computed, and no score is left unwritten."""
+@pytest.mark.parametrize("value", [math.nan, math.inf, -math.inf])
+def test_not_finite(value):
+    """A NaN or infinite key spoils its own column and the rows whose logit with
+    it is NaN or +inf, which then count nowhere; rows that see it at -inf give it
+    no weight.  The other tiles are still computed, and no score is left
+    unwritten."""
     g = torch.Generator().manual_seed(5)
     q, k = _values("normal", (1, 4, 16, 128), g), _values("normal", (1, 1, 300, 128), g)
-    k[0, 0, 70, 5] = float("nan")
+    k[0, 0, 70, 5] = value
     ev = Evictor(1, 300, 4, 1, 128, 16, 1)
     ev.scores.fill_(-1.0)
     ev.score(q.cuda(), k.cuda(), [300])
-    s = ev.scores[0, 0, :284].cpu()
+    s = ev.scores[0, 0, :284].cpu().double()
+    logits = q[0].reshape(64, 128).double() @ k[0, 0].double().T / math.sqrt(128)
+    logits.masked_fill_(torch.arange(300)[None, :] > torch.arange(284, 300).repeat(4)[:, None], -math.inf)
+    counts = logits[:, 70] == -math.inf
+    ref = torch.softmax(logits[counts], dim=-1).sum(dim=0)[:284]
     assert torch.isnan(s[70])
-    s[70] = 0.0
-    assert torch.equal(s, torch.zeros_like(s))
+    keep = torch.arange(284) != 70
+    assert bool(((s - ref)[keep].abs() <= REL * ref[keep]).all())
+    assert 16 < int(counts.sum()) < 48 or math.isnan(value)
 
 
 def _check_raw(q, k, L, w):
